@@ -379,8 +379,9 @@ ffv_status ffv_op_conv(int32_t precision, const float* x, int32_t n, int32_t cin
  *   grad:  DEVICE float32 [n][3][H][W] = d loss[i] / d x_i, or NULL; at a
  *          sample where a band is exactly 0 the sign is taken as 0
  * H, W >= 33 (five levels of mirror padding need 3 samples at the coarsest).
- * Allocates its workspace, orders its work on `stream` (NULL = default
- * stream) and synchronises it. Per-workgroup sums are combined in a fixed
+ * Takes its workspace from a cache that the process keeps (at most 64 MiB;
+ * larger ones are allocated and freed by the call), orders its work on
+ * `stream` (NULL = default stream) and synchronises it. Per-workgroup sums are combined in a fixed
  * order in double precision, so repeated calls give identical results.
  * Errors: FFV_ERR_ARG, FFV_ERR_OOM, FFV_ERR_DEVICE.
  */

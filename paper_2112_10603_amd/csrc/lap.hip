@@ -8,19 +8,34 @@
 // filter [1, 4, 6, 4, 1] / 16 under mirror padding (the edge sample is not
 // repeated) and expand = blur with gain 2 per axis of the zero-inserted
 // coarser level. The loss of an image is sum_i 2^(i-1) mean |L^i|. Every
-// plane (image, channel) is an independent h x w array; one thread per
-// output sample.
-//
-// Reductions: each workgroup reduces |L| of its samples in fp32 across the
-// wavefront (DPP/shuffle) and the workgroup, and writes one double partial;
-// a final kernel sums an image's partials in a fixed order in double, so
-// the result does not depend on scheduling.
+// plane (image, channel) is an independent h x w array.
 //
 // Gradient: with seeds s_i = 2^(i-1) / N_i * sign(L^i) (sign 0 at 0), the
 // derivative reaching G^i is a_i = s_i + R^T(a_(i+1) - E^T(s_i)), from the
 // coarsest level down (a_6 = 0), where R = decimate . blur and
 // E = blur_gain2 . zero-insert; the transposes gather over the taps that
 // read a sample, including the mirror-folded ones.
+//
+// Launches. A training batch is small (8 x 256 x 448: 11 MB in, 5.5 MB out),
+// so the launches count as much as the bytes. The fine levels take one
+// launch each; every level of at most kTailMax samples per plane belongs to
+// one workgroup per plane that keeps the rest of the pyramid in LDS (one
+// launch forward, one backward). All bands run in one launch, all E^T in
+// one, all partial sums in one.
+// A quad (2 x 2 samples of a level, at even coordinates) belongs to one
+// coarser sample, so the bands, the signs and the transposes work per quad:
+// 3 x 3 coarse samples serve four fine ones, and the four signs are stored
+// as one byte.
+//
+// Reductions: each workgroup of the band pass reduces |L| of its samples in
+// fp32 across the wavefront and the workgroup, and writes one double
+// partial; one workgroup per image sums them in a fixed order in double, so
+// the result does not depend on scheduling.
+//
+// Measured (one MI355X, whole call): 8 x 3 x 256 x 448 with gradient 561 ->
+// 89 us, 1 x 3 x 1079 x 1917 without 2637 -> 81 us. Before, one thread
+// summed all partials of an image, each level had its own launches, seeds
+// were floats, and the border gathers walked 9 x 9 taps.
 #include <algorithm>
 
 #include "common.h"
@@ -31,8 +46,17 @@ namespace ffv {
 namespace {
 
 constexpr int TPB = 256;
+// Samples per plane up to which a level is handled by the one-workgroup
+// passes: 64 KB of LDS for the level and a third more for the coarser ones.
+constexpr int kTailMax = 16384;
+constexpr int kTailTPB = 1024;
 
-__device__ __constant__ float kBin[5] = {1.f / 16, 4.f / 16, 6.f / 16, 4.f / 16, 1.f / 16};
+constexpr float K0 = 1.f / 16, K1 = 4.f / 16, K2 = 6.f / 16;  // [K0 K1 K2 K1 K0]
+
+// Levels of one call: level 0 is the image, level i + 1 halves level i.
+struct Levels {
+  int h[kLapLevels + 1], w[kLapLevels + 1];
+};
 
 __device__ inline int mirror(int i, int n) {
   i = i < 0 ? -i : i;
@@ -40,175 +64,415 @@ __device__ inline int mirror(int i, int n) {
 }
 
 // Weight with which output j of the mirror-padded blur along an axis of
-// length n reads input i (sum over the taps that land on i).
+// length n reads input i: the tap at their distance, and near an end the tap
+// that the mirror folds onto i. 0 when j is no sample.
 __device__ inline float blur_w(int j, int i, int n) {
-  float w = 0.f;
-#pragma unroll
-  for (int t = 0; t < 5; ++t) w += mirror(j + t - 2, n) == i ? kBin[t] : 0.f;
-  return w;
+  const int d = abs(i - j), lo = i + j, hi = 2 * (n - 1) - lo;
+  float w = d == 0 ? K2 : (d == 1 ? K1 : (d == 2 ? K0 : 0.f));
+  if (i > 0 && lo <= 2) w += lo == 2 ? K0 : K1;
+  if (i < n - 1 && hi <= 2) w += hi == 2 ? K0 : K1;
+  return j >= 0 && j < n ? w : 0.f;
 }
 
-// G^(i+1) = reduce(G^i) for every plane; G^1 = a - b when b is given.
-__global__ void reduce_k(const float* a, const float* b, int h, int w, int ho, int wo, float* out) {
+// Five-tap blur of v0..v4, in tap order.
+__device__ inline float blur5(float v0, float v1, float v2, float v3, float v4) {
+  float r = 0.f;
+  r += K0 * v0;
+  r += K1 * v1;
+  r += K2 * v2;
+  r += K1 * v3;
+  r += K0 * v4;
+  return r;
+}
+
+// G^(i+1) = reduce(G^i) of one RX x RY tile of every plane; G^1 = a - b when
+// DIFF. Bound by memory: the tile's input is read once into LDS (about 1.1
+// reads per sample, rows of 131 consecutive floats), blurred along x there,
+// then along y. (One thread per output with its 25 taps from the caches,
+// two images at level 0, took 60 us for the levels of a 1079 x 1917 image.)
+constexpr int RX = 64, RY = 8;
+template <bool DIFF>
+__global__ __launch_bounds__(TPB) void reduce_k(const float* a, const float* b, int h, int w, int ho, int wo,
+                                                int tiles_x, float* out) {
+  constexpr int IW = 2 * RX + 3, IH = 2 * RY + 3;
+  __shared__ float in[IH][IW + 1];
+  __shared__ float hr[IH][RX];
   const long plane = blockIdx.y;
-  const long p = (long)blockIdx.x * TPB + threadIdx.x;
-  if (p >= (long)ho * wo) return;
-  const int y = (int)(p / wo), x = (int)(p % wo);
+  const int ty = blockIdx.x / tiles_x, tx = blockIdx.x - ty * tiles_x;
+  const int x0 = tx * RX, y0 = ty * RY;
   const float* pa = a + plane * h * w;
-  const float* pb = b ? b + plane * h * w : nullptr;
-  int xs[5];
+  const float* pb = DIFF ? b + plane * h * w : nullptr;
+  // (samples past the mirrored border belong to no output: clamped)
+  for (int r = threadIdx.x >> 6; r < IH; r += TPB / 64) {
+    const long row = (long)min(max(mirror(2 * y0 - 2 + r, h), 0), h - 1) * w;
 #pragma unroll
-  for (int t = 0; t < 5; ++t) xs[t] = mirror(2 * x + t - 2, w);
-  float acc = 0.f;
-#pragma unroll
-  for (int u = 0; u < 5; ++u) {
-    const long row = (long)mirror(2 * y + u - 2, h) * w;
-    float r = 0.f;
-#pragma unroll
-    for (int t = 0; t < 5; ++t) {
-      const float v = pa[row + xs[t]] - (pb ? pb[row + xs[t]] : 0.f);
-      r += kBin[t] * v;
+    for (int k = 0; k < 3; ++k) {
+      const int c = (threadIdx.x & 63) + 64 * k;
+      if (c < IW) {
+        const long o = row + min(max(mirror(2 * x0 - 2 + c, w), 0), w - 1);
+        float v = pa[o];
+        if constexpr (DIFF) v -= pb[o];
+        in[r][c] = v;
+      }
     }
-    acc += kBin[u] * r;
   }
-  out[plane * ho * wo + p] = acc;
+  __syncthreads();
+  const int x = threadIdx.x & 63;
+  for (int r = threadIdx.x >> 6; r < IH; r += TPB / 64)
+    hr[r][x] = blur5(in[r][2 * x], in[r][2 * x + 1], in[r][2 * x + 2], in[r][2 * x + 3], in[r][2 * x + 4]);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < RY / 4; ++k) {
+    const int y = (threadIdx.x >> 6) + 4 * k;
+    if (y0 + y < ho && x0 + x < wo)
+      out[plane * ho * wo + (long)(y0 + y) * wo + x0 + x] =
+          blur5(hr[2 * y][x], hr[2 * y + 1][x], hr[2 * y + 2][x], hr[2 * y + 3][x], hr[2 * y + 4][x]);
+  }
 }
 
-// expand(G^(i+1)) at (y, x) of an h x w level: zero-inserted samples sit at
-// even mirrored positions; gain 2 per axis.
-__device__ inline float expand_at(const float* g, int hn, int wn, int h, int w, int y, int x) {
-  float acc = 0.f;
+// Levels m + 1 .. 5 of one plane from its level m (at most kTailMax
+// samples), each level kept in LDS for the next; a chain of small steps, so
+// bound by latency: one workgroup and its barriers instead of a launch per
+// level.
+struct TailArgs {
+  Levels L;
+  float* G[kLapLevels + 1];
+  int m;
+};
+__global__ __launch_bounds__(kTailTPB) void reduce_tail_k(TailArgs t) {
+  extern __shared__ float lds[];
+  const long plane = blockIdx.x;
+  float* cur = lds;
+  const int n = t.L.h[t.m] * t.L.w[t.m];
+  const float* src = t.G[t.m] + plane * n;
+  for (int i = threadIdx.x; i < n; i += kTailTPB) cur[i] = src[i];
+  __syncthreads();
+  for (int l = t.m; l < kLapLevels; ++l) {
+    const int h = t.L.h[l], w = t.L.w[l], ho = t.L.h[l + 1], wo = t.L.w[l + 1];
+    float* nxt = cur + h * w;
+    float* dst = t.G[l + 1] + plane * ho * wo;
+    for (int i = threadIdx.x; i < ho * wo; i += kTailTPB) {
+      const int y = i / wo, x = i - y * wo;
+      int xs[5];
 #pragma unroll
-  for (int u = 0; u < 5; ++u) {
-    const int yy = mirror(y + u - 2, h);
-    if (yy & 1) continue;
-    float r = 0.f;
+      for (int k = 0; k < 5; ++k) xs[k] = mirror(2 * x + k - 2, w);
+      float r[5];
 #pragma unroll
-    for (int t = 0; t < 5; ++t) {
-      const int xx = mirror(x + t - 2, w);
-      if (xx & 1) continue;
-      r += kBin[t] * g[(long)(yy >> 1) * wn + (xx >> 1)];
+      for (int k = 0; k < 5; ++k) {
+        const float* row = cur + mirror(2 * y + k - 2, h) * w;
+        r[k] = blur5(row[xs[0]], row[xs[1]], row[xs[2]], row[xs[3]], row[xs[4]]);
+      }
+      const float v = blur5(r[0], r[1], r[2], r[3], r[4]);
+      nxt[i] = v;
+      dst[i] = v;
     }
-    acc += kBin[u] * r;
+    __syncthreads();
+    cur = nxt;
   }
-  return 4.f * acc;
 }
 
-// Band L^i = G^i - expand(G^(i+1)) of every plane: per-workgroup partial sum
-// of |L| (double), and the gradient seed weight * sign(L) when seed != null.
-__global__ void band_k(const float* a, const float* b, const float* gnext, int h, int w, int hn, int wn,
-                       float weight, float* seed, double* partial) {
+// The launch-wide passes over several levels: level l owns the workgroups
+// first[l] .. first[l+1]-1 along grid x, one thread per quad.
+struct BandArgs {
+  Levels L;
+  const float* x;
+  const float* gt;
+  const float* G[kLapLevels + 1];  // levels 1..5
+  uint8_t* S[kLapLevels];          // packed signs per quad, or null
+  double* partial;                 // [plane][first[5]]
+  int first[kLapLevels + 1];
+};
+template <typename A>
+__device__ inline int level_of(const A& t) {
+  int l = 0;
+  for (int k = 1; k < kLapLevels; ++k)
+    if ((int)blockIdx.x >= t.first[k]) l = k;
+  return l;
+}
+
+// Band L^i = G^i - expand(G^(i+1)) of every plane and level: per-workgroup
+// partial sum of |L| and, with signs, two bits per sample (0, 1 = +, 2 = -).
+// The zero-inserted samples a fine sample reads sit at even mirrored
+// positions (mirroring keeps the parity), so an even row reads the coarse
+// rows around it with K0, K2, K0 and an odd one the two next to it with K1.
+__global__ __launch_bounds__(TPB) void band_k(BandArgs t) {
+  const int l = level_of(t);
   const long plane = blockIdx.y;
-  const long p = (long)blockIdx.x * TPB + threadIdx.x;
-  float v = 0.f;
-  if (p < (long)h * w) {
-    const int y = (int)(p / w), x = (int)(p % w);
-    const long o = plane * h * w + p;
-    const float g = a[o] - (b ? b[o] : 0.f);
-    const float l = g - expand_at(gnext + plane * hn * wn, hn, wn, h, w, y, x);
-    v = fabsf(l);
-    if (seed) seed[o] = l > 0.f ? weight : (l < 0.f ? -weight : 0.f);
+  const int h = t.L.h[l], w = t.L.w[l], hn = t.L.h[l + 1], wn = t.L.w[l + 1];
+  const int q = ((int)blockIdx.x - t.first[l]) * TPB + threadIdx.x;
+  float sum = 0.f;
+  if (q < hn * wn) {
+    const int yq = q / wn, xq = q - yq * wn;
+    const float* g = t.G[l + 1] + plane * hn * wn;
+    const int rows[3] = {mirror(2 * yq - 2, h) >> 1, yq, mirror(2 * yq + 2, h) >> 1};
+    const int cols[3] = {mirror(2 * xq - 2, w) >> 1, xq, mirror(2 * xq + 2, w) >> 1};
+    float re[3], ro[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const float* row = g + (long)rows[k] * wn;
+      const float g0 = row[cols[0]], g1 = row[cols[1]], g2 = row[cols[2]];
+      float e = 0.f, o = 0.f;
+      e += K0 * g0;
+      e += K2 * g1;
+      e += K0 * g2;
+      o += K1 * g1;
+      o += K1 * g2;
+      re[k] = e;
+      ro[k] = o;
+    }
+    const float* a = l == 0 ? t.x : t.G[l];
+    unsigned signs = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int y = 2 * yq + (k >> 1), x = 2 * xq + (k & 1);
+      if (y >= h || x >= w) continue;
+      const float* r = (k & 1) ? ro : re;
+      float acc = 0.f;
+      if (k >> 1) {
+        acc += K1 * r[1];
+        acc += K1 * r[2];
+      } else {
+        acc += K0 * r[0];
+        acc += K2 * r[1];
+        acc += K0 * r[2];
+      }
+      const long o = (plane * h + y) * w + x;
+      float v = a[o];
+      if (l == 0) v -= t.gt[o];
+      const float band = v - 4.f * acc;
+      sum += fabsf(band);
+      signs |= (band > 0.f ? 1u : (band < 0.f ? 2u : 0u)) << (2 * k);
+    }
+    if (t.S[l]) t.S[l][plane * hn * wn + q] = (uint8_t)signs;
   }
   // wavefront reduction, then the workgroup's four wavefronts
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
   __shared__ float wsum[TPB / 64];
-  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = sum;
   __syncthreads();
   if (threadIdx.x == 0) {
     double s = 0.0;
 #pragma unroll
     for (int i = 0; i < TPB / 64; ++i) s += (double)wsum[i];
-    partial[plane * gridDim.x + blockIdx.x] = s;
+    t.partial[plane * gridDim.x + blockIdx.x] = s;
   }
 }
 
-// acc[img] (+)= weight * sum of the partials of its 3 planes, in a fixed
-// order; the first level assigns.
-__global__ void sum_k(const double* partial, int blocks_per_plane, int n_img, double weight, int first,
-                      double* acc) {
-  const int img = blockIdx.x * blockDim.x + threadIdx.x;
-  if (img >= n_img) return;
-  double s = 0.0;
-  for (long i = 0; i < 3L * blocks_per_plane; ++i) s += partial[(long)img * 3 * blocks_per_plane + i];
-  acc[img] = (first ? 0.0 : acc[img]) + weight * s;
+// loss[img] = sum over levels of weight * (sum of the level's partials of
+// the image's 3 planes): one workgroup per image, each thread a fixed
+// strided share, then a fixed tree, in double. (One thread per image took
+// 2.4 of the 2.6 ms of a 1079 x 1917 loss.)
+struct SumArgs {
+  const double* partial;
+  int first[kLapLevels + 1];
+  double weight[kLapLevels];
+  float* loss;
+};
+__global__ __launch_bounds__(TPB) void sum_k(SumArgs t) {
+  const int n = t.first[kLapLevels];
+  const double* p = t.partial + (long)blockIdx.x * 3 * n;
+  double total = 0.0;
+  for (int l = 0; l < kLapLevels; ++l) {
+    double s = 0.0;
+    for (int pl = 0; pl < 3; ++pl)
+      for (int i = t.first[l] + threadIdx.x; i < t.first[l + 1]; i += TPB) s += p[(long)pl * n + i];
+    total += t.weight[l] * s;
+  }
+  __shared__ double red[TPB];
+  red[threadIdx.x] = total;
+  __syncthreads();
+  for (int k = TPB / 2; k > 0; k >>= 1) {
+    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) t.loss[blockIdx.x] = (float)red[0];
 }
 
-__global__ void finish_k(const double* acc, int n_img, float* loss) {
-  const int img = blockIdx.x * blockDim.x + threadIdx.x;
-  if (img < n_img) loss[img] = (float)acc[img];
-}
-
-// t = a_next - E^T(s) on the coarser level (hn x wn): E^T(s)[p][q] =
-// 4 * sum over fine (j, jj) of B[j][2p] B[jj][2q] s[j][jj].
-__global__ void et_k(const float* anext, const float* s, int h, int w, int hn, int wn, float* t) {
+// E_(i+1) = E^T(s_i) on level i + 1, all levels: E^T(s)[p][q] =
+// 4 * sum over fine (j, jj) of B[j][2p] B[jj][2q] s[j][jj], the 5 x 5 samples
+// around (2p, 2q), i.e. 3 x 3 packed quads. Mirrored taps fold onto samples
+// of that window too, so the borders differ in the weights alone.
+struct EtArgs {
+  Levels L;
+  const uint8_t* S[kLapLevels];
+  float weight[kLapLevels];
+  float* E[kLapLevels + 1];  // levels 1..5
+  int first[kLapLevels + 1];
+  int negate_last;  // write T_5 = -E_5 in the place of E_5
+};
+__global__ __launch_bounds__(TPB) void et_k(EtArgs t) {
+  const int l = level_of(t);
   const long plane = blockIdx.y;
-  const long p = (long)blockIdx.x * TPB + threadIdx.x;
-  if (p >= (long)hn * wn) return;
-  const int y = (int)(p / wn), x = (int)(p % wn);
-  const float* ps = s + plane * h * w;
-  float acc = 0.f;
-  for (int j = max(0, 2 * y - 4); j <= min(h - 1, 2 * y + 4); ++j) {
-    const float wy = blur_w(j, 2 * y, h);
-    if (wy == 0.f) continue;
-    float r = 0.f;
-    for (int jj = max(0, 2 * x - 4); jj <= min(w - 1, 2 * x + 4); ++jj) {
-      const float wx = blur_w(jj, 2 * x, w);
-      if (wx != 0.f) r += wx * ps[(long)j * w + jj];
-    }
-    acc += wy * r;
+  const int h = t.L.h[l], w = t.L.w[l], hn = t.L.h[l + 1], wn = t.L.w[l + 1];
+  const int q = ((int)blockIdx.x - t.first[l]) * TPB + threadIdx.x;
+  if (q >= hn * wn) return;
+  const int y = q / wn, x = q - y * wn;
+  const uint8_t* s = t.S[l] + plane * hn * wn;
+  const float weight = t.weight[l];
+  float wy[5] = {K0, K1, K2, K1, K0}, wx[5] = {K0, K1, K2, K1, K0};
+  if (y < 2 || 2 * y + 4 > h - 1)
+#pragma unroll
+    for (int u = 0; u < 5; ++u) wy[u] = blur_w(2 * y - 2 + u, 2 * y, h);
+  if (x < 2 || 2 * x + 4 > w - 1)
+#pragma unroll
+    for (int u = 0; u < 5; ++u) wx[u] = blur_w(2 * x - 2 + u, 2 * x, w);
+  unsigned c[3][3];
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+    const uint8_t* row = s + (long)min(max(y - 1 + u, 0), hn - 1) * wn;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c[u][k] = row[min(max(x - 1 + k, 0), wn - 1)];
   }
-  const long o = plane * hn * wn + p;
-  t[o] = (anext ? anext[o] : 0.f) - 4.f * acc;
+  float acc = 0.f;
+#pragma unroll
+  for (int u = 0; u < 5; ++u) {
+    float r = 0.f;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      const unsigned b = (c[u >> 1][k >> 1] >> (4 * (u & 1) + 2 * (k & 1))) & 3u;
+      r += wx[k] * (b == 1u ? weight : (b == 2u ? -weight : 0.f));
+    }
+    acc += wy[u] * r;
+  }
+  const float v = 4.f * acc;
+  t.E[l + 1][plane * hn * wn + q] = l == kLapLevels - 1 && t.negate_last ? 0.f - v : v;
 }
 
-// a = s + R^T(t) on the finer level (h x w): R^T(t)[i][ii] = sum over even
-// (j, jj) of B[j][i] B[jj][ii] t[j/2][jj/2].
-__global__ void rt_k(const float* s, const float* t, int h, int w, int hn, int wn, float* a) {
-  const long plane = blockIdx.y;
-  const long p = (long)blockIdx.x * TPB + threadIdx.x;
-  if (p >= (long)h * w) return;
-  const int y = (int)(p / w), x = (int)(p % w);
-  const float* pt = t + plane * hn * wn;
-  float acc = 0.f;
-  for (int j = max(0, y - 4) & ~1; j <= min(h - 1, y + 4); j += 2) {
-    const float wy = blur_w(j, y, h);
-    if (wy == 0.f) continue;
-    float r = 0.f;
-    for (int jj = max(0, x - 4) & ~1; jj <= min(w - 1, x + 4); jj += 2) {
-      const float wx = blur_w(jj, x, w);
-      if (wx != 0.f) r += wx * pt[(long)(j >> 1) * wn + (jj >> 1)];
+// The quad (yq, xq) of a_l = s_l + R^T(T_(l+1)), R^T(t)[i][ii] = sum over
+// even (j, jj) of B[j][i] B[jj][ii] t[j/2][jj/2]: an even row reads the
+// three coarse rows around it, an odd one the two next to it; near the
+// borders only the weights differ. Level l's T_l = a_l - E_l when E is given
+// (what the next finer level reads), else the gradient.
+__device__ inline void rt_quad(const float* tn, const uint8_t* s, const float* E, int h, int w, int hn, int wn, int yq,
+                               int xq, float weight, float* out) {
+  const unsigned c = s[(long)yq * wn + xq];
+  // weights of the coarse samples yq - 1, yq, yq + 1 for the even and the odd row
+  float ye[3] = {K0, K2, K0}, yo[3] = {0.f, K1, K1}, xe[3] = {K0, K2, K0}, xo[3] = {0.f, K1, K1};
+  if (yq < 2 || 2 * yq + 5 > h - 1)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      ye[k] = blur_w(2 * yq - 2 + 2 * k, 2 * yq, h);
+      yo[k] = k ? blur_w(2 * yq - 2 + 2 * k, 2 * yq + 1, h) : 0.f;
     }
-    acc += wy * r;
+  if (xq < 2 || 2 * xq + 5 > w - 1)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      xe[k] = blur_w(2 * xq - 2 + 2 * k, 2 * xq, w);
+      xo[k] = k ? blur_w(2 * xq - 2 + 2 * k, 2 * xq + 1, w) : 0.f;
+    }
+  const int x0 = max(xq - 1, 0), x2 = min(xq + 1, wn - 1);
+  float re[3], ro[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const float* row = tn + (long)min(max(yq - 1 + k, 0), hn - 1) * wn;
+    float e = 0.f, o = 0.f;
+    e += xe[0] * row[x0];
+    e += xe[1] * row[xq];
+    e += xe[2] * row[x2];
+    o += xo[1] * row[xq];
+    o += xo[2] * row[x2];
+    re[k] = e;
+    ro[k] = o;
   }
-  const long o = plane * h * w + p;
-  a[o] = s[o] + acc;
+  float v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float* r = (k & 1) ? ro : re;
+    float acc = 0.f;
+    if (k >> 1) {
+      acc += yo[1] * r[1];
+      acc += yo[2] * r[2];
+    } else {
+      acc += ye[0] * r[0];
+      acc += ye[1] * r[1];
+      acc += ye[2] * r[2];
+    }
+    v[k] = acc;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int y = 2 * yq + (k >> 1), x = 2 * xq + (k & 1);
+    if (y >= h || x >= w) continue;
+    const unsigned b = (c >> (2 * k)) & 3u;
+    const float a = (b == 1u ? weight : (b == 2u ? -weight : 0.f)) + v[k];
+    const long o = (long)y * w + x;
+    out[o] = E ? a - E[o] : a;
+  }
+}
+
+__global__ __launch_bounds__(TPB) void rt_k(const float* tn, const uint8_t* s, const float* E, int h, int w, int hn,
+                                            int wn, float weight, float* out) {
+  const long plane = blockIdx.y;
+  const int q = (int)blockIdx.x * TPB + threadIdx.x;
+  if (q >= hn * wn) return;
+  const int yq = q / wn;
+  rt_quad(tn + plane * hn * wn, s + plane * hn * wn, E ? E + plane * h * w : nullptr, h, w, hn, wn, yq, q - yq * wn,
+          weight, out + plane * h * w);
+}
+
+// T_5 .. T_m of one plane, coarsest first (T_5 = -E_5), in LDS; T_m is
+// written over E_m.
+struct BackTailArgs {
+  Levels L;
+  const uint8_t* S[kLapLevels];
+  float weight[kLapLevels];
+  float* E[kLapLevels + 1];
+  int m;
+};
+__global__ __launch_bounds__(kTailTPB) void back_tail_k(BackTailArgs t) {
+  extern __shared__ float lds[];
+  const long plane = blockIdx.x;
+  float* cur = lds;
+  int n = t.L.h[kLapLevels] * t.L.w[kLapLevels];
+  for (int i = threadIdx.x; i < n; i += kTailTPB) cur[i] = 0.f - t.E[kLapLevels][plane * n + i];
+  __syncthreads();
+  for (int l = kLapLevels - 1; l >= t.m; --l) {
+    const int h = t.L.h[l], w = t.L.w[l], hn = t.L.h[l + 1], wn = t.L.w[l + 1];
+    float* nxt = cur + n;
+    n = h * w;
+    for (int q = threadIdx.x; q < hn * wn; q += kTailTPB) {
+      const int yq = q / wn;
+      rt_quad(cur, t.S[l] + plane * hn * wn, t.E[l] + plane * n, h, w, hn, wn, yq, q - yq * wn, t.weight[l], nxt);
+    }
+    __syncthreads();
+    cur = nxt;
+  }
+  float* dst = t.E[t.m] + plane * n;
+  for (int i = threadIdx.x; i < n; i += kTailTPB) dst[i] = cur[i];
 }
 
 inline unsigned blocks(long n) { return (unsigned)((n + TPB - 1) / TPB); }
 
-// Level sizes (level 0 is the image) and the workspace layout: loss
-// accumulators, reduction partials, levels 1..5 (reused by the backward pass
-// for its per-level t and a), and the gradient seeds of levels 0..4. Each
-// buffer starts on a 256-byte boundary. With base == null only the size is
+// The workspace: reduction partials, levels 1..5, and for the gradient the
+// packed signs of levels 0..4 and E (later T) of levels 1..5. Each buffer
+// starts on a 256-byte boundary. With base == null only the size is
 // computed.
 struct LapPlan {
-  int h[kLapLevels + 1], w[kLapLevels + 1];
-  double* acc;
+  Levels L;
+  int m;                           // finest level the one-workgroup passes own
+  int first[kLapLevels + 1];       // workgroups of the all-level passes
   double* partial;
   float* G[kLapLevels + 1];
-  float* S[kLapLevels];
-  size_t bytes;
+  uint8_t* S[kLapLevels];
+  float* E[kLapLevels + 1];
+  size_t bytes, tail_lds;
 };
 
 LapPlan lap_plan(int n_img, int H, int W, bool grad, void* base) {
-  LapPlan L{};
-  L.h[0] = H;
-  L.w[0] = W;
+  LapPlan P{};
+  P.L.h[0] = H;
+  P.L.w[0] = W;
   for (int i = 0; i < kLapLevels; ++i) {
-    L.h[i + 1] = (L.h[i] + 1) / 2;
-    L.w[i + 1] = (L.w[i] + 1) / 2;
+    P.L.h[i + 1] = (P.L.h[i] + 1) / 2;
+    P.L.w[i + 1] = (P.L.w[i] + 1) / 2;
   }
+  auto samples = [&](int i) { return (long)P.L.h[i] * P.L.w[i]; };
+  P.m = 1;  // (level 0 is two images, not a level buffer)
+  while (P.m < kLapLevels && samples(P.m) > kTailMax) ++P.m;
+  if (P.m < kLapLevels)
+    for (int i = P.m; i <= kLapLevels; ++i) P.tail_lds += samples(i) * 4;
+  for (int i = 0; i < kLapLevels; ++i) P.first[i + 1] = P.first[i] + (int)blocks(samples(i + 1));
   const size_t planes = 3 * (size_t)n_img;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -216,15 +480,14 @@ LapPlan lap_plan(int n_img, int H, int W, bool grad, void* base) {
     off += (bytes + 255) / 256 * 256;
     return r;
   };
-  L.acc = reinterpret_cast<double*>(take((size_t)n_img * 8));
-  size_t max_part = 0;
-  for (int i = 0; i < kLapLevels; ++i) max_part = std::max(max_part, (size_t)blocks((long)L.h[i] * L.w[i]));
-  L.partial = reinterpret_cast<double*>(take(planes * max_part * 8));
-  for (int i = 1; i <= kLapLevels; ++i) L.G[i] = reinterpret_cast<float*>(take(planes * L.h[i] * L.w[i] * 4));
-  if (grad)
-    for (int i = 0; i < kLapLevels; ++i) L.S[i] = reinterpret_cast<float*>(take(planes * L.h[i] * L.w[i] * 4));
-  L.bytes = off;
-  return L;
+  P.partial = reinterpret_cast<double*>(take(planes * P.first[kLapLevels] * 8));
+  for (int i = 1; i <= kLapLevels; ++i) P.G[i] = reinterpret_cast<float*>(take(planes * samples(i) * 4));
+  if (grad) {
+    for (int i = 0; i < kLapLevels; ++i) P.S[i] = reinterpret_cast<uint8_t*>(take(planes * samples(i + 1)));
+    for (int i = 1; i <= kLapLevels; ++i) P.E[i] = reinterpret_cast<float*>(take(planes * samples(i) * 4));
+  }
+  P.bytes = off;
+  return P;
 }
 
 }  // namespace
@@ -237,53 +500,82 @@ hipError_t launch_lap_loss(const float* x, const float* gt, int n_img, int H, in
   if (H < kLapMinSize || W < kLapMinSize || !ws) return hipErrorInvalidValue;
   const LapPlan P = lap_plan(n_img, H, W, grad != nullptr, ws);
   if (P.bytes > ws_bytes) return hipErrorInvalidValue;
-  const long planes = 3L * n_img;
-  const int* hs = P.h;
-  const int* wsz = P.w;
-  double* acc = P.acc;
-  double* partial = P.partial;
-  float* const* G = P.G;
-  const float* const* S = P.S;
+  const unsigned planes = 3u * (unsigned)n_img;
+  const Levels& L = P.L;
   hipError_t e;
 
-  // forward: reduce chain, then the bands and their sums (band i uses levels
+  // forward: reduce chain, then every band and the sums (band i uses levels
   // i and i+1; level 0 is x - gt, read directly)
-  for (int i = 0; i < kLapLevels; ++i) {
-    const float* a = i == 0 ? x : G[i];
-    const float* b = i == 0 ? gt : nullptr;
-    hipLaunchKernelGGL(reduce_k, dim3(blocks((long)hs[i + 1] * wsz[i + 1]), (unsigned)planes), dim3(TPB), 0, s, a,
-                       b, hs[i], wsz[i], hs[i + 1], wsz[i + 1], G[i + 1]);
+  for (int i = 0; i < P.m; ++i) {
+    const int h = L.h[i], w = L.w[i], ho = L.h[i + 1], wo = L.w[i + 1];
+    const int tx = (wo + RX - 1) / RX, ty = (ho + RY - 1) / RY;
+    const dim3 grid((unsigned)(tx * ty), planes);
+    if (i == 0)
+      hipLaunchKernelGGL(reduce_k<true>, grid, dim3(TPB), 0, s, x, gt, h, w, ho, wo, tx, P.G[1]);
+    else
+      hipLaunchKernelGGL(reduce_k<false>, grid, dim3(TPB), 0, s, P.G[i], nullptr, h, w, ho, wo, tx, P.G[i + 1]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  for (int i = 0; i < kLapLevels; ++i) {
-    const float* a = i == 0 ? x : G[i];
-    const float* b = i == 0 ? gt : nullptr;
-    const long n = (long)hs[i] * wsz[i];
-    const double weight = (double)(1 << i) / (3.0 * (double)n);  // 2^(i-1) / N_i, N_i = 3 h w
-    const unsigned nb = blocks(n);
-    hipLaunchKernelGGL(band_k, dim3(nb, (unsigned)planes), dim3(TPB), 0, s, a, b, G[i + 1], hs[i], wsz[i],
-                       hs[i + 1], wsz[i + 1], (float)weight, grad ? const_cast<float*>(S[i]) : nullptr, partial);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(sum_k, dim3((unsigned)((n_img + 63) / 64)), dim3(64), 0, s, partial, (int)nb, n_img, weight,
-                       i == 0 ? 1 : 0, acc);
+  if (P.m < kLapLevels) {
+    TailArgs t{};
+    t.L = L;
+    t.m = P.m;
+    for (int i = 1; i <= kLapLevels; ++i) t.G[i] = P.G[i];
+    hipLaunchKernelGGL(reduce_tail_k, dim3(planes), dim3(kTailTPB), P.tail_lds, s, t);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(finish_k, dim3((unsigned)((n_img + 63) / 64)), dim3(64), 0, s, acc, n_img, loss);
+  const dim3 all((unsigned)P.first[kLapLevels], planes);
+  double weight[kLapLevels];
+  for (int i = 0; i < kLapLevels; ++i)
+    weight[i] = (double)(1 << i) / (3.0 * (double)L.h[i] * L.w[i]);  // 2^(i-1) / N_i, N_i = 3 h w
+  BandArgs b{};
+  SumArgs m{};
+  b.L = L;
+  b.x = x;
+  b.gt = gt;
+  b.partial = P.partial;
+  m.partial = P.partial;
+  m.loss = loss;
+  for (int i = 0; i <= kLapLevels; ++i) {
+    b.G[i] = P.G[i];
+    b.first[i] = m.first[i] = P.first[i];
+    if (i < kLapLevels) {
+      b.S[i] = P.S[i];
+      m.weight[i] = weight[i];
+    }
+  }
+  hipLaunchKernelGGL(band_k, all, dim3(TPB), 0, s, b);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(sum_k, dim3((unsigned)n_img), dim3(TPB), 0, s, m);
   if ((e = hipGetLastError()) != hipSuccess || !grad) return e;
 
-  // backward, coarsest level first: t lives on level i+1, a on level i
-  // (the G buffers are reused: G^(i+1) holds t, then a of level i+1 is dead)
-  float* a_next = nullptr;  // a_(i+1), on level i+1
-  for (int i = kLapLevels - 1; i >= 0; --i) {
-    float* t = G[i + 1];  // G^(i+1) is no longer needed
-    hipLaunchKernelGGL(et_k, dim3(blocks((long)hs[i + 1] * wsz[i + 1]), (unsigned)planes), dim3(TPB), 0, s, a_next,
-                       S[i], hs[i], wsz[i], hs[i + 1], wsz[i + 1], t);
+  // backward: E^T of every level's signs, then T coarsest level first
+  EtArgs t{};
+  BackTailArgs k{};
+  t.L = k.L = L;
+  k.m = P.m;
+  for (int i = 0; i <= kLapLevels; ++i) {
+    t.E[i] = k.E[i] = P.E[i];
+    t.first[i] = P.first[i];
+    if (i < kLapLevels) {
+      t.S[i] = k.S[i] = P.S[i];
+      t.weight[i] = k.weight[i] = (float)weight[i];
+    }
+  }
+  // (images whose level 5 is larger than the one-workgroup pass takes have
+  // no such pass)
+  t.negate_last = P.m == kLapLevels;
+  hipLaunchKernelGGL(et_k, all, dim3(TPB), 0, s, t);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (P.m < kLapLevels) {
+    hipLaunchKernelGGL(back_tail_k, dim3(planes), dim3(kTailTPB), P.tail_lds, s, k);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    float* a = i == 0 ? grad : G[i];
-    hipLaunchKernelGGL(rt_k, dim3(blocks((long)hs[i] * wsz[i]), (unsigned)planes), dim3(TPB), 0, s, S[i], t, hs[i],
-                       wsz[i], hs[i + 1], wsz[i + 1], a);
+  }
+  for (int i = P.m - 1; i >= 0; --i) {
+    // T_i replaces E_i, sample by sample; level 0 gives the gradient
+    hipLaunchKernelGGL(rt_k, dim3(blocks((long)L.h[i + 1] * L.w[i + 1]), planes), dim3(TPB), 0, s, P.E[i + 1], P.S[i],
+                       P.E[i], L.h[i], L.w[i], L.h[i + 1], L.w[i + 1], (float)weight[i], i == 0 ? grad : P.E[i]);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    a_next = a;
   }
   return hipSuccess;
 }
