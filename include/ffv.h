@@ -43,7 +43,9 @@ typedef enum {
 } ffv_status;
 
 typedef enum {
-  FFV_FP32 = 0,      /* convolutions on fp32 MFMA, fp32 activations */
+  FFV_FP32 = 0,      /* fp32 activations and accumulation; every product of a
+                        convolution exact to below 2^-26 (operands split into three
+                        bf16 parts for the matrix cores) */
   FFV_BF16 = 1,      /* convolutions on bf16 MFMA with fp32 accumulation */
   FFV_FP8_E4M3 = 2   /* VIBlock 128/256-channel convs in fp8 e4m3 (per-channel activation
                         scales folded into per-output-channel weight scales, fp32
@@ -141,6 +143,9 @@ ffv_status ffv_interpolate_recursive(ffv_net* net, const ffv_pair* views, int32_
  * timed with HIP events on the net's stream, and keeps the fastest per
  * (layer, fp8 or not, output grid, images per launch). Later calls whose
  * launches match use those choices; captured graphs are dropped.
+ * Launches of the direct-weight kernel (small grids, and every fp32 layer)
+ * have nothing to choose: they get an entry that names their default tile,
+ * and run that kernel whatever the table says.
  * *n_tuned (nullable) = launch shapes tuned. Takes seconds at 1080p batch
  * sizes. Errors as ffv_interpolate.
  */
@@ -336,8 +341,9 @@ ffv_status ffv_stitch_cluster(const float* real_view, const float* const* left,
  * precision: FFV_FP32 or FFV_BF16 (inputs and weights rounded to bf16, fp32
  * accumulation and output), optionally or'ed with FFV_OP_ACT_OUT: the layer
  * writes its output in the activation dtype (bf16 for FFV_BF16), as the
- * network's layers do, and y receives those values widened to float32. n_tile (0 = the layer's default, else 256, 128,
- * 64 or 32 output channels per workgroup, or 1 = the halo-reuse kernel:
+ * network's layers do, and y receives those values widened to float32. n_tile (0 = the layer's default,
+ * which with tile_w = 0 is the tile the network would take, the direct-weight
+ * kernel included; else 256, 128, 64 or 32 output channels per workgroup, or 1 = the halo-reuse kernel:
  * 32 channels of a 16x16 pixel block, for stride-1 convs whose input
  * channels are a multiple of the K step; 2 and 3 = the 128- and 256-channel
  * tiles reading each channel slice's input halo once, for stride-1 and
@@ -354,7 +360,8 @@ ffv_status ffv_stitch_cluster(const float* real_view, const float* const* left,
  * cannot run the layer gives FFV_ERR_DEVICE) and tile_w (0 =
  * default, else the
  * width of the 256-pixel block of a workgroup, a divisor of 256) pick the
- * kernel variant, as autotuning does; every choice gives the same result.
+ * kernel variant, as autotuning does; every choice gives the same result (fp32:
+ * the direct-weight kernel and the others agree to fp32 rounding).
  * Allocates temporaries; synchronises `stream`.
  */
 ffv_status ffv_op_conv(int32_t precision, const float* x, int32_t n, int32_t cin, int32_t h,

@@ -406,14 +406,63 @@ ffv_status op_conv_run(const OpConvScratch* scratch, int32_t precision, const fl
   plan_layer(L);
   const int ho = L.transposed ? 2 * h : (h - 1) / stride + 1;
   const int wo = L.transposed ? 2 * w : (w - 1) / stride + 1;
-  std::vector<uint8_t> packed = pack_layer(L, dt);
   const size_t e = dtype_size(dt);
   // output as the network's layers write it (activation dtype), or float
   const DType out_dt = act_out ? dt : DType::F32;
+  ConvArgs a{};
+  a.in_img_stride = (long)h * w * L.cin_pad;
+  a.in_ld = L.cin_pad;
+  a.Hi = h;
+  a.Wi = w;
+  a.out_img_stride = (long)ho * wo * cout;
+  a.out_ld = cout;
+  a.Ho = L.transposed ? h : ho;
+  a.Wo = L.transposed ? w : wo;
+  a.Hout = ho;
+  a.Wout = wo;
+  a.cin_pad = L.cin_pad;
+  a.K = L.K;
+  a.K_pad = L.K_pad;
+  a.cout = cout;
+  a.cout_pad = L.cout_pad;
+  a.n_rows = L.rows;
+  a.n_img = n;
+  a.stride = L.transposed ? 1 : stride;
+  a.transposed = L.mode;
+  a.relu = relu ? 1 : 0;
+  a.out_f32 = out_dt == DType::F32 ? 1 : 0;
+  a.accumulate = 0;
+  a.taps = L.mode == 1 ? 4 : 9;
+  a.tile_w = tile_w > 0 ? tile_w : conv_tile_width(a.Ho, a.Wo);
   // the call's device buffers: NHWC input, packed weights, bias, NHWC output
   // and a zero block for taps outside the image
-  const size_t sizes[5] = {(size_t)n * h * w * L.cin_pad * e, packed.size(), (size_t)cout * 4,
-                           (size_t)n * ho * wo * cout * dtype_size(out_dt), 256};
+  size_t sizes[5] = {(size_t)n * h * w * L.cin_pad * e, 0, (size_t)cout * 4,
+                     (size_t)n * ho * wo * cout * dtype_size(out_dt), 256};
+  auto need_with = [&](size_t weights) {
+    size_t need = (weights + 255) / 256 * 256;
+    for (size_t b : sizes) need += (b + 255) / 256 * 256;
+    return need;
+  };
+  // The default tile as the network chooses it: the direct-weight kernel
+  // where it takes the launch and its larger weights fit the no-allocation
+  // entry point's scratch too (so that both entry points give the same bits).
+  DirectTile direct = DirectTile::None;
+  std::vector<uint8_t> packed;
+  if (n_tile == 0 && tile_w == 0 && direct_layer(L, dt)) {
+    a.wfrag = x;  // any non-null pointer: only the shape counts here
+    int tw = 0;
+    direct = conv_direct_tile(dt, a, &tw);
+    a.wfrag = nullptr;
+    if (direct != DirectTile::None) {
+      packed = pack_direct(L, dt);
+      if (need_with(packed.size()) <= FFV_OP_NOALLOC_SCRATCH_BYTES)
+        a.tile_w = tw;
+      else
+        direct = DirectTile::None;
+    }
+  }
+  if (direct == DirectTile::None) packed = pack_layer(L, dt);
+  sizes[1] = packed.size();
   void* buf[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   hipError_t err = hipSuccess;
   if (scratch) {
@@ -443,36 +492,12 @@ ffv_status op_conv_run(const OpConvScratch* scratch, int32_t precision, const fl
   if (err == hipSuccess) err = hipMemcpyAsync(bd, bias, (size_t)cout * 4, hipMemcpyHostToDevice, s);
   if (err == hipSuccess) err = launch_pack_nhwc(x, n, cin, h, w, xin, L.cin_pad, dt, s);
   if (err == hipSuccess) {
-    ConvArgs a{};
     a.in = xin;
-    a.in_img_stride = (long)h * w * L.cin_pad;
-    a.in_ld = L.cin_pad;
-    a.Hi = h;
-    a.Wi = w;
-    a.wgt = wd;
+    a.wgt = direct == DirectTile::None ? wd : nullptr;
+    a.wfrag = direct == DirectTile::None ? nullptr : wd;
     a.bias = (const float*)bd;
     a.out = yo;
-    a.out_img_stride = (long)ho * wo * cout;
-    a.out_ld = cout;
-    a.Ho = L.transposed ? h : ho;
-    a.Wo = L.transposed ? w : wo;
-    a.Hout = ho;
-    a.Wout = wo;
-    a.cin_pad = L.cin_pad;
-    a.K = L.K;
-    a.K_pad = L.K_pad;
-    a.cout = cout;
-    a.cout_pad = L.cout_pad;
-    a.n_rows = L.rows;
-    a.n_img = n;
-    a.stride = L.transposed ? 1 : stride;
-    a.transposed = L.mode;
-    a.relu = relu ? 1 : 0;
-    a.out_f32 = out_dt == DType::F32 ? 1 : 0;
-    a.accumulate = 0;
-    a.taps = L.mode == 1 ? 4 : 9;
     a.zero = zr;
-    a.tile_w = tile_w > 0 ? tile_w : conv_tile_width(a.Ho, a.Wo);
     ConvTile tile = L.tile;
     if (n_tile == 256) tile = ConvTile::N256;
     if (n_tile == 128) tile = ConvTile::N128;
@@ -494,7 +519,7 @@ ffv_status op_conv_run(const OpConvScratch* scratch, int32_t precision, const fl
       tile = n_tile == 6 ? ConvTile::S32 : (n_tile == 7 ? ConvTile::S64 : ConvTile::S128);
       a.tile_w = 16;
     }
-    err = launch_conv(dt, tile, a, s);
+    err = direct == DirectTile::None ? launch_conv(dt, tile, a, s) : launch_conv_direct(dt, direct, a, s);
   }
   for (int i = 0; err == hipSuccess && i < n; ++i)
     err = launch_extract((const char*)yo + (size_t)i * ho * wo * cout * dtype_size(out_dt), out_dt, cout, cout,

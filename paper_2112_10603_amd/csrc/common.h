@@ -62,6 +62,7 @@ struct ConvArgs {
   int taps;             // taps in K (9, or 4 for one transposed phase)
   int tile_w;           // width of the 2-D pixel block of an M tile (divides the M tile)
   const void* zero;     // >= 16 bytes of zeros (read for taps outside the image)
+  const void* wfrag;    // the weights in fragment order (conv_direct.h), or null
 };
 
 // One launch of the implicit-GEMM kernel over up to kMax groups of images
@@ -112,6 +113,23 @@ bool conv_resident_ok(DType dt, const ConvArgs& a, int bn);
 // Whether the stride-2 resident kernel with a bn-channel N tile (32, 64 or
 // 128) can run a launch.
 bool conv_resident_s2_ok(DType dt, const ConvArgs& a, int bn);
+
+// Tiles (pixels x GEMM columns) of the kernel whose weights go straight into
+// registers (conv_direct.h). Every tile computes the same values.
+enum class DirectTile : int { None = 0, M64N64, M64N128, M128N32, M128N64, M128N128, M128N256, M256N128 };
+// The direct tile for a launch and its pixel block width (*tile_w), or None
+// when the tiles of ConvTile serve it better or the kernel cannot run it.
+// a.wfrag only needs to be non-null. fp32 launches take a direct tile
+// wherever the kernel can run them, whatever the number of images, so that a
+// view does not depend on its batch.
+DirectTile conv_direct_tile(DType dt, const ConvArgs& a, int* tile_w);
+hipError_t launch_conv_direct(DType dt, DirectTile tile, const ConvArgs& a, hipStream_t s);
+hipError_t launch_direct_f32(DirectTile tile, const ConvArgs& a, hipStream_t s);
+hipError_t launch_direct_bf16(DirectTile tile, const ConvArgs& a, hipStream_t s);
+hipError_t launch_direct_f8(DirectTile tile, const ConvArgs& a, hipStream_t s);
+// Bytes past the end of the weights in fragment order that the kernel's
+// loads may run ahead into (contents unused).
+constexpr size_t kDirectPad = 64 << 10;
 
 hipError_t launch_conv(DType dt, ConvTile tile, const ConvArgs& a, hipStream_t s);
 // One launch over n (1 .. ConvGroup::kMax) groups of images of the same

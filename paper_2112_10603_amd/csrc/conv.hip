@@ -2,6 +2,7 @@
 // used by the library, one per N-tile class, and of the halo-reuse kernel
 // (conv_halo.h). All use 128-byte K steps (conv_k_step), which the weight
 // packing's K order depends on.
+#include "conv_direct.h"
 #include "conv_halo.h"
 #include "conv_kernel.h"
 #include "conv_resident.h"
@@ -76,6 +77,27 @@ hipError_t launch_t(ConvTile tile, const ConvArgs* g, int n, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+// Whether a tile's halo buffers fit LDS at a.tile_w.
+template <typename T>
+bool direct_fits_t(const ConvArgs& a, DirectTile tile) {
+  using namespace convk;
+  switch (tile) {
+    case DirectTile::M64N64: return direct_plan<T, 256, 64>(a, 64).nbuf > 0;
+    case DirectTile::M64N128: return direct_plan<T, 256, 128>(a, 64).nbuf > 0;
+    case DirectTile::M128N32: return direct_plan<T, 256, 32>(a, 128).nbuf > 0;
+    case DirectTile::M128N64: return direct_plan<T, 256, 64>(a, 128).nbuf > 0;
+    case DirectTile::M128N128: return direct_plan<T, 256, 128>(a, 128).nbuf > 0;
+    case DirectTile::M128N256: return direct_plan<T, 512, 256>(a, 128).nbuf > 0;
+    case DirectTile::M256N128: return direct_plan<T, 512, 128>(a, 256).nbuf > 0;
+    default: return false;
+  }
+}
+
+bool direct_fits(DType dt, const ConvArgs& a, DirectTile tile) {
+  return dt == DType::F32 ? direct_fits_t<float>(a, tile)
+                          : (dt == DType::BF16 ? direct_fits_t<bf16>(a, tile) : direct_fits_t<f8>(a, tile));
+}
+
 }  // namespace
 
 int conv_k_step(DType dt) { return dt == DType::F32 ? 32 : (dt == DType::BF16 ? 64 : 128); }
@@ -100,6 +122,104 @@ bool conv_halo_ok(DType dt, const ConvArgs& a) {
   ConvArgs b = a;
   b.tile_w = convk::Halo::TW;
   return convk::halo_ok(b, conv_k_step(dt));
+}
+
+DirectTile conv_direct_tile(DType dt, const ConvArgs& a0, int* tile_w) {
+  using namespace convk;
+  const bool can = dt == DType::F32 ? direct_ok<float>(a0) : (dt == DType::BF16 ? direct_ok<bf16>(a0) : direct_ok<f8>(a0));
+  if (!can) return DirectTile::None;
+  struct Cand {
+    DirectTile tile;
+    int bm, bn;
+  };
+  const int rows = a0.n_rows;
+  // The least padded block width of a candidate whose halo fits, and its
+  // workgroups; 0 when none fits.
+  auto blocks = [&](const Cand& c, int* tw_best) -> long {
+    long best = 0;
+    for (int tw : {16, 8, 32}) {
+      ConvArgs a = a0;
+      a.tile_w = tw;
+      const bool fits = c.bm % tw == 0 && direct_fits(dt, a, c.tile);
+      if (!fits) continue;
+      const int th = c.bm / tw;
+      const long n = (long)a.n_img * ((a.Ho + th - 1) / th) * ((a.Wo + tw - 1) / tw) * (a.taps == 4 ? 4 : 1) *
+                     ((rows + c.bn - 1) / c.bn);
+      if (best == 0 || n < best) {
+        best = n;
+        *tw_best = tw;
+      }
+    }
+    return best;
+  };
+  const Cand m64n64{DirectTile::M64N64, 64, 64}, m64n128{DirectTile::M64N128, 64, 128},
+      m128n32{DirectTile::M128N32, 128, 32}, m128n64{DirectTile::M128N64, 128, 64},
+      m128n128{DirectTile::M128N128, 128, 128}, m128n256{DirectTile::M128N256, 128, 256},
+      m256n128{DirectTile::M256N128, 256, 128};
+  int tw = 0;
+  long n;
+  if (dt == DType::F32) {
+    // One workgroup per compute unit: the smallest tile whose workgroups fit
+    // the 256 units in one round, else the largest (its weight fragments
+    // feed the most MFMAs). 256 -> 256, 3x3, us of 64x64 / 64x128 / 128x128
+    // tiles and of the best fp32 MFMA tile: 45x80 (228 workgroups of 64x64)
+    // 33 / 42 / 68 / 80; 90x160 (226 of 128x128) 132 / 99 / 90 / 162;
+    // 270x480 1098 / 915 / 823 / 1255. Narrow layers: the narrowest tile
+    // (128 -> 5 transposed at 360x640: 32 columns 170, 64 columns 214).
+    if (rows <= 32) {
+      if (blocks(m128n32, tile_w) > 0) return m128n32.tile;
+    } else if (rows <= 64) {
+      n = blocks(m64n64, &tw);
+      if (n > 0 && n <= 256) {
+        *tile_w = tw;
+        return m64n64.tile;
+      }
+      if (blocks(m128n64, tile_w) > 0) return m128n64.tile;
+    } else {
+      for (const Cand& c : {m64n64, m64n128}) {
+        n = blocks(c, &tw);
+        if (n > 0 && n <= 256) {
+          *tile_w = tw;
+          return c.tile;
+        }
+      }
+      if (blocks(m128n128, tile_w) > 0) return m128n128.tile;
+    }
+    // (a halo of 2 x 64 pixels at stride 2 always fits)
+    return blocks(m64n64, tile_w) > 0 ? m64n64.tile : DirectTile::None;
+  }
+  // bf16, fp8: launches of at most one round of workgroups, smallest tile
+  // first; beyond that the tiles of ConvTile move fewer weight bytes. us of
+  // 64x64 / 128x64 / 128x128 / 128x256 tiles and of the best ConvTile, 256 ->
+  // 256, 3x3, bf16: 16x16 8.8 / 11 / 16 / 25 / 14; 45x80 (228 workgroups of
+  // 64x64) 10.0 / 12 / 17 / 26 / 15; 68x120 (136 of 128x128) 23 / 24 / 18 /
+  // 27 / 29; 135x240 (254 of 128x256) 59 / 50 / 42 / 39 / 58; 180x320 109 /
+  // 97 / 79 / 71 / 66. 256x128 tiles, transposed 256 -> 128 at 90x160: 22
+  // against 25. fp8 has the 64x64 tile only (the wider ones spill), worth it
+  // up to two rounds: 45x80 7.9 against 10.4, 68x120 (510 workgroups) 20.5
+  // against 29.3 for the default tile and 19.6 for the best.
+  const Cand* list[5] = {&m64n64, nullptr, nullptr, nullptr, nullptr};
+  if (dt == DType::BF16) {
+    list[1] = &m128n64;
+    if (rows > 64) list[2] = &m128n128;
+    if (rows > 64 && a0.taps == 4) list[3] = &m256n128;
+    if (rows > 128 && a0.transposed == 0 && a0.stride == 1) list[4] = &m128n256;
+  }
+  for (const Cand* c : list) {
+    if (!c) continue;
+    n = blocks(*c, &tw);
+    if (n > 0 && n <= (dt == DType::FP8 ? 512 : 256)) {
+      *tile_w = tw;
+      return c->tile;
+    }
+  }
+  return DirectTile::None;
+}
+
+hipError_t launch_conv_direct(DType dt, DirectTile tile, const ConvArgs& a, hipStream_t s) {
+  if (a.n_img <= 0 || a.Ho <= 0 || a.Wo <= 0) return hipSuccess;
+  if (dt == DType::F32) return launch_direct_f32(tile, a, s);
+  return dt == DType::FP8 ? launch_direct_f8(tile, a, s) : launch_direct_bf16(tile, a, s);
 }
 
 int conv_tile_width(int Ho, int Wo) {

@@ -190,13 +190,14 @@ void plan_layer(Layer& L) {
 // Weights (file layout w_file) rearranged as the conv kernel reads them, in
 // float: [phase][cout_pad][k_pad] with the kernel's K order for K step bk.
 static std::vector<float> pack_layer_f(const Layer& L, int bk, int k_pad,
-                                       const std::vector<float>& w_file) {
+                                       const std::vector<float>& w_file, bool slices = false) {
   const int phases = L.mode == 1 ? 4 : 1;
   const int taps = L.mode == 1 ? 4 : 9;
   const size_t n = (size_t)phases * L.cout_pad * k_pad;
   // K position of (tap, channel): channel-slice major when the channel count
   // is a multiple of the kernel's K step (as the kernel walks K), else tap major.
-  const bool slice_major = L.cin_pad % bk == 0;
+  // `slices` asks for it anyway, with the last slice zero-padded to bk.
+  const bool slice_major = slices || L.cin_pad % bk == 0;
   auto kpos = [&](int tap, int c) {
     if (!slice_major) return tap * L.cin_pad + c;
     return ((c / bk) * taps + tap) * bk + (c % bk);
@@ -289,6 +290,60 @@ std::vector<uint8_t> pack_layer(const Layer& L, DType dt) {
   return bytes;
 }
 
+// Packed bf16 or fp8 rows ([phase][cout_pad][k_pad], slice-major K) in
+// fragment order: per phase and 32 rows, per K step of 128 bytes, the 1 KiB
+// MFMA operands a wave reads one after another (lane l: row l % 32, a 16-byte
+// chunk of lane half l / 32's share of the step).
+static std::vector<uint8_t> fragment_order(const Layer& L, DType dt, int k_pad, const std::vector<uint8_t>& packed) {
+  const size_t e = dtype_size(dt), row_bytes = (size_t)k_pad * e;
+  const int phases = L.mode == 1 ? 4 : 1, steps = (L.mode == 1 ? 4 : 9) * L.cin_pad / conv_k_step(dt);
+  const size_t rows = (size_t)phases * L.cout_pad;
+  std::vector<uint8_t> f(rows * steps * 128 + kDirectPad, 0);
+  uint8_t* q = f.data();
+  for (size_t r0 = 0; r0 < rows; r0 += 32)
+    for (int st = 0; st < steps; ++st)
+      for (int c = 0; c < 4; ++c)
+        for (int lane = 0; lane < 64; ++lane, q += 16)
+          std::memcpy(q, &packed[(r0 + lane % 32) * row_bytes + (size_t)st * 128 + ((lane / 32) * 4 + c) * 16], 16);
+  return f;
+}
+
+bool direct_layer(const Layer& L, DType dt) {
+  return L.name != "unet.head" && (dt == DType::F32 || L.cin_pad % conv_k_step(dt) == 0);
+}
+
+std::vector<uint8_t> pack_direct(const Layer& L, DType dt) {
+  if (dt != DType::F32) return fragment_order(L, dt, L.K_pad, pack_layer(L, dt));
+  // fp32: three bf16 parts per weight, w = h + m + l exactly
+  const int bk = conv_k_step(dt), taps = L.mode == 1 ? 4 : 9, slices = (L.cin_pad + bk - 1) / bk;
+  const int k_pad = slices * taps * bk;
+  const std::vector<float> p = pack_layer_f(L, bk, k_pad, L.w_host, true);
+  const size_t rows = (size_t)(L.mode == 1 ? 4 : 1) * L.cout_pad;
+  std::vector<uint8_t> f(rows * k_pad * 6 + kDirectPad, 0);
+  uint16_t* q = reinterpret_cast<uint16_t*>(f.data());
+  auto widen = [](uint16_t b) {
+    const uint32_t u = (uint32_t)b << 16;
+    float v;
+    std::memcpy(&v, &u, 4);
+    return v;
+  };
+  for (size_t r0 = 0; r0 < rows; r0 += 32)
+    for (int st = 0; st < slices * taps; ++st)
+      for (int g = 0; g < 2; ++g, q += 3 * 512)
+        for (int lane = 0; lane < 64; ++lane) {
+          const float* src = &p[(r0 + lane % 32) * k_pad + (size_t)st * bk + (lane / 32) * 16 + g * 8];
+          for (int e = 0; e < 8; ++e) {
+            const uint16_t h = f2bf(src[e]);
+            const float r = src[e] - widen(h);
+            const uint16_t m = f2bf(r);
+            q[lane * 8 + e] = h;
+            q[512 + lane * 8 + e] = m;
+            q[1024 + lane * 8 + e] = f2bf(r - widen(m));
+          }
+        }
+  return f;
+}
+
 // ----------------------------------------------------------------- Net
 
 Geo Geo::of(int H, int W) {
@@ -311,7 +366,7 @@ Net::~Net() {
   drop_graphs();
   for (auto& kv : layers_) {
     Layer& L = kv.second;
-    for (void* p : {(void*)L.w_dev, (void*)L.b_dev, L.w8_dev, (void*)L.w8_scale, (void*)L.out_scale,
+    for (void* p : {(void*)L.w_dev, L.w_frag, (void*)L.b_dev, L.w8_dev, L.w8_frag, (void*)L.w8_scale, (void*)L.out_scale,
                     (void*)L.amax})
       if (p) hipFree(p);
   }
@@ -383,6 +438,11 @@ Status Net::init(const std::string& path, int precision, int device, hipStream_t
       FFV_TRY(dev_alloc(&L.w_dev, packed.size(), "weights"));
       FFV_TRY(check(hipMemcpy(L.w_dev, packed.data(), packed.size(), hipMemcpyHostToDevice),
                     "copy weights"));
+      if (direct_layer(L, dt_)) {
+        packed = pack_direct(L, dt_);
+        FFV_TRY(dev_alloc(&L.w_frag, packed.size(), "weights"));
+        FFV_TRY(check(hipMemcpy(L.w_frag, packed.data(), packed.size(), hipMemcpyHostToDevice), "copy weights"));
+      }
     }
     FFV_TRY(dev_alloc((void**)&L.b_dev, L.b_host.size() * 4, "bias"));
     FFV_TRY(check(hipMemcpy(L.b_dev, L.b_host.data(), L.b_host.size() * 4, hipMemcpyHostToDevice),
@@ -609,6 +669,7 @@ Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long 
   a.Hi = Hi;
   a.Wi = Wi;
   a.wgt = in_fp8 ? L.w8_dev : L.w_dev;
+  a.wfrag = in_fp8 ? L.w8_frag : L.w_frag;
   a.w_scale = in_fp8 ? L.w8_scale : nullptr;
   a.out_scale = out_fp8 ? L.out_scale : nullptr;
   a.amax = calibrating_ ? L.amax : nullptr;
@@ -667,6 +728,10 @@ Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long 
       a.tile_w = 16;
     }
   }
+  // small grids, and every fp32 layer: the direct-weight kernel (whatever the
+  // tuning table says: the table chooses among the other tiles)
+  int direct_w = 0;
+  const DirectTile direct = conv_direct_tile(kdt, a, &direct_w);
   if (!tuned_.empty() || recording_) {
     const TuneKey key{L.name, in_fp8 ? 1 : 0, a.Ho, a.Wo, n_img};
     auto it = tuned_.find(key);
@@ -674,7 +739,7 @@ Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long 
       tile = it->second.tile;
       a.tile_w = it->second.tile_w;
     }
-    if (recording_) recs_.push_back(TuneRec{key, a, kdt});
+    if (recording_) recs_.push_back(TuneRec{key, a, kdt, direct != DirectTile::None});
   }
   if (in_ld < L.cin_pad || in_ld % (in_fp8 ? 16 : 8) != 0) return Status::err(-4, "conv input stride");
   if ((in_fp8 && !L.w8_dev) || (out_fp8 && !L.out_scale)) return Status::err(-7, "fp8 layer not quantised");
@@ -739,13 +804,33 @@ Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long 
       }
       gflops += 2.0 * vg.n * (double)b.Hout * b.Wout * L.cout * L.cin * (L.transposed ? 4.0 : 9.0);
     }
+    // groups the direct kernel takes are launched one by one, the others together
     prof_begin(x);
-    Status st = check(launch_conv_grouped(kdt, gt, g, x.n_groups, x.s), L.name.c_str());
+    Status st = Status::ok();
+    int rest = 0;
+    for (int j = 0; j < x.n_groups && st.good(); ++j) {
+      ConvArgs b = g[j];
+      int tw = 0;
+      const DirectTile d = conv_direct_tile(kdt, b, &tw);
+      if (d == DirectTile::None) {
+        g[rest++] = g[j];
+        continue;
+      }
+      b.tile_w = tw;
+      st = check(launch_conv_direct(kdt, d, b, x.s), L.name.c_str());
+    }
+    if (st.good() && rest > 0) st = check(launch_conv_grouped(kdt, gt, g, rest, x.s), L.name.c_str());
     prof_end(x, cls, gflops);
     return st;
   }
   prof_begin(x);
-  Status st = check(launch_conv(kdt, tile, a, x.s), L.name.c_str());
+  Status st;
+  if (direct != DirectTile::None) {
+    a.tile_w = direct_w;
+    st = check(launch_conv_direct(kdt, direct, a, x.s), L.name.c_str());
+  } else {
+    st = check(launch_conv(kdt, tile, a, x.s), L.name.c_str());
+  }
   prof_end(x, cls, flops);
   return st;
 }
@@ -1338,6 +1423,11 @@ Status Net::quantize_vib_layers() {
       for (size_t i = 0; i < pf.size(); ++i) q[i] = f2f8(pf[i]);
       if (!L.w8_dev) FFV_TRY(check(hipMalloc(&L.w8_dev, q.size()), "hipMalloc fp8 weights"));
       FFV_TRY(check(hipMemcpy(L.w8_dev, q.data(), q.size(), hipMemcpyHostToDevice), "copy fp8 weights"));
+      if (direct_layer(L, DType::FP8)) {
+        const std::vector<uint8_t> f = fragment_order(L, DType::FP8, k_pad, q);
+        if (!L.w8_frag) FFV_TRY(check(hipMalloc(&L.w8_frag, f.size()), "hipMalloc fp8 weights"));
+        FFV_TRY(check(hipMemcpy(L.w8_frag, f.data(), f.size(), hipMemcpyHostToDevice), "copy fp8 weights"));
+      }
       if (!L.w8_scale)
         FFV_TRY(check(hipMalloc((void**)&L.w8_scale, sizeof(float) * L.cout), "hipMalloc w scale"));
       FFV_TRY(check(hipMemcpy(L.w8_scale, ws.data(), sizeof(float) * L.cout, hipMemcpyHostToDevice),
@@ -1375,6 +1465,10 @@ Status Net::autotune(const float* const* left, const float* const* right, int n_
   for (size_t r = 0; res.good() && r < recs_.size(); ++r) {
     const TuneRec& rec = recs_[r];
     if (found.count(rec.key)) continue;
+    if (rec.direct) {
+      found[rec.key] = TuneVal{layers_.at(rec.key.layer).tile, rec.a.tile_w};
+      continue;
+    }
     const int rows32 = round_up(rec.a.n_rows, 32);
     long min_area = -1;
     for (int tw : widths) {

@@ -31,11 +31,13 @@ struct Layer {
   std::vector<float> w_host;  // file layout
   std::vector<float> b_host;
   void* w_dev = nullptr;      // packed [phase][cout_pad][K_pad], activation dtype
+  void* w_frag = nullptr;     // the same weights in fragment order (conv_direct.h), or null
   float* b_dev = nullptr;
   // FP8 (VIBlock 128/256-channel layers): fp8 weights with the producer's
   // activation scales folded in, the per-output-channel dequant scale, the
   // output quantisation scale (1 / activation scale) and calibration amax.
   void* w8_dev = nullptr;
+  void* w8_frag = nullptr;
   float* w8_scale = nullptr;
   float* out_scale = nullptr;
   float* amax = nullptr;
@@ -55,6 +57,10 @@ void plan_layer(Layer& L);
 // Pack L.w_host for dtype dt into a host byte buffer laid out as the conv
 // kernel reads it.
 std::vector<uint8_t> pack_layer(const Layer& L, DType dt);
+// Whether the direct kernel has a weight layout for a layer, and L.w_host in
+// that layout (fragment order, kDirectPad bytes of padding at the end).
+bool direct_layer(const Layer& L, DType dt);
+std::vector<uint8_t> pack_direct(const Layer& L, DType dt);
 
 struct KernelStat {
   long launches = 0;
@@ -264,6 +270,7 @@ class Net {
     TuneKey key;
     ConvArgs a;
     DType dt;
+    bool direct;  // the direct kernel runs it: nothing to tune
   };
   std::vector<TuneRec> recs_;
 
