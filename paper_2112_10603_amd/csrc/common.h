@@ -171,10 +171,12 @@ struct ViewDesc {
   int wp, h, w, pad;
 };
 
-hipError_t launch_ingest(const float* const* src, int n_cam, int H, int W, int Hp, int Wp,
-                         float* X4, void* Xa, DType dt, hipStream_t s);
-hipError_t launch_resample4(const float* in, int n_img, int Hi, int Wi, float* out, int Ho, int Wo,
-                            hipStream_t s);
+// Cameras' padded images (X4: 4 floats per pixel, Xa: 8 activations) and
+// their quarter- (L0) and half-size (L1) copies, at those byte offsets of
+// camera blocks `stride` bytes apart; src is a device table of n_cam planar
+// images.
+hipError_t launch_ingest(const float* const* src, int n_cam, int H, int W, int Hp, int Wp, char* block, long stride,
+                         size_t X4, size_t Xa, size_t L0, size_t L1, DType dt, hipStream_t s);
 hipError_t launch_assemble0(const ViewDesc* views, int n_views, const CamDev* cams, int h, int w,
                             void* x, int ld, DType dt, int t_plane, hipStream_t s);
 hipError_t launch_transition(const ViewDesc* views, int n_views, const CamDev* cams, int level,
@@ -182,13 +184,15 @@ hipError_t launch_transition(const ViewDesc* views, int n_views, const CamDev* c
                              float* FM, DType dt, int t_plane, hipStream_t s);
 hipError_t launch_final(const ViewDesc* views, int n_views, const CamDev* cams, const float* FM,
                         int h, int w, float* I2, void* x0u, int ld, DType dt, hipStream_t s);
-// Flow pyramid level k+1 from level k (k = 0: full resolution) of every
-// view: in/out strided by the launch's level sizes h x w and h/2 x w/2.
-hipError_t launch_flow_down(const float* in, int in_ld, const ViewDesc* views, int n_img, int k, int h, int w,
-                            float* out, hipStream_t s);
-hipError_t launch_ctx_warp(const ViewDesc* views, int n_views, const CamDev* cams, int level, int C,
-                           const float* flow, int h, int w, void* dst, int dst_ld,
-                           long dst_img_stride, DType dt, hipStream_t s);
+// Flow pyramid (levels 1..4 of every view, 4 floats per pixel) from the
+// full-resolution flow and mask; slots strided by the launch's padded size
+// h x w and its halves.
+hipError_t launch_flow_pyramid(const float* FM, const ViewDesc* views, int n_img, int h, int w, float* const F[4],
+                               hipStream_t s);
+// Context features of levels 1..4 (C[k] channels per side) warped by the
+// flow pyramid into dst[k] (left, then right; pixel stride ld[k]).
+hipError_t launch_ctx_warp(const ViewDesc* views, int n_views, const CamDev* cams, int h, int w, const int C[4],
+                           float* const flow[4], void* const dst[4], const int ld[4], DType dt, hipStream_t s);
 // Multi-view cluster frame: [left block | real view | right block], each
 // side g*g views box-downscaled by g and tiled in raster order.
 struct StitchArgs {

@@ -175,7 +175,7 @@ struct Conv {
   static_assert(FM >= 1 && FN >= 1, "wave tile >= 32x32");
   static_assert(NT % CH == 0, "chunk of a thread is fixed");
   static_assert(CH == 4 || CH == 8, "64- or 128-byte steps");
-  static_assert(STAGES >= 2 && STAGES <= 8, "ring of 2 to 8 stages");
+  static_assert(STAGES >= 2 && STAGES <= 4, "ring of 2 to 4 stages");
   static_assert(STAGES == 2 || (A_VECS % NT == 0 && B_VECS % NT == 0),
                 "a deeper ring needs the same load count in every wave");
 

@@ -850,21 +850,12 @@ Status Net::build_cameras(const Exec& x, const Geo& g, const float* const* src_d
   if (cs % 256 != 0) return Status::err(-4, "camera stride");
   char* b0 = blocks[0];
   const long P = g.P;
-  // ingest, padding and the image pyramid, one camera per launch
-  for (int i = 0; i < n_cam; ++i) {
-    prof_begin(x);
-    FFV_TRY(check(launch_ingest(src_dev + i, 1, g.H, g.W, g.Hp, g.Wp, (float*)(blocks[i] + c.X4),
-                                blocks[i] + c.Xa, dt_, x.s),
-                  "ingest"));
-    FFV_TRY(check(launch_resample4((const float*)(blocks[i] + c.X4), 1, g.Hp, g.Wp,
-                                   (float*)(blocks[i] + c.L0), g.Hp / 4, g.Wp / 4, x.s),
-                  "resample L0"));
-    FFV_TRY(check(launch_resample4((const float*)(blocks[i] + c.X4), 1, g.Hp, g.Wp,
-                                   (float*)(blocks[i] + c.L1), g.Hp / 2, g.Wp / 2, x.s),
-                  "resample L1"));
-    prof_end(x, "pixel", (double)g.H * g.W * 12 + P * (16.0 + 8 * e) + 2 * P * 16.0 +
-                             (P / 16 + P / 4) * 16.0);
-  }
+  // ingest, padding and the image pyramid
+  prof_begin(x);
+  FFV_TRY(check(launch_ingest(src_dev, n_cam, g.H, g.W, g.Hp, g.Wp, b0, cs, c.X4, c.Xa, c.L0, c.L1, dt_, x.s),
+                "ingest"));
+  prof_end(x, "pixel",
+           n_cam * ((double)g.H * g.W * 12 + P * (16.0 + 8 * e) + 2 * P * 16.0 + (P / 16 + P / 4) * 16.0));
   if (!context) return Status::ok();
   // ContextNet batched over the cameras: image stride = camera block stride
   const int cw[4] = {B / 2, B, 2 * B, 4 * B};
@@ -967,26 +958,22 @@ Status Net::run_views(const Exec& x, const ViewPlan& p, const CamDev* cams,
 
   // flow pyramid and context warps
   {
-    const float* src = (const float*)x.at(p.FM[2]);
-    int ld = 8, h = g.Hp, w = g.Wp;
     const int cw[4] = {B / 2, B, 2 * B, 4 * B};
     const int lv_ld[4] = {3 * B, 6 * B, 12 * B, 16 * B};
     const int lv_off[4] = {2 * B, 4 * B, 8 * B, 8 * B};
+    float* fp[4];
+    void* dst[4];
+    double bytes = 0.0;
     for (int k = 0; k < 4; ++k) {
-      const int ho = h / 2, wo = w / 2;
-      const long Pk = (long)ho * wo;
-      prof_begin(x);
-      FFV_TRY(check(launch_flow_down(src, ld, views, nv, k, h, w, (float*)x.at(p.Fp[k]), x.s), "flow_down"));
-      FFV_TRY(check(launch_ctx_warp(views, nv, cams, k, cw[k], (const float*)x.at(p.Fp[k]), ho, wo,
-                                    x.at(p.lvl[k]) + lv_off[k] * e, lv_ld[k], Pk * lv_ld[k], dt_, x.s),
-                    "ctx_warp"));
-      prof_end(x, "pixel", (double)nv * ((double)h * w * 16 + Pk * 16 + 2 * Pk * 16 +
-                                         2.0 * Pk * cw[k] * e * 2));
-      src = (const float*)x.at(p.Fp[k]);
-      ld = 4;
-      h = ho;
-      w = wo;
+      fp[k] = (float*)x.at(p.Fp[k]);
+      dst[k] = x.at(p.lvl[k]) + lv_off[k] * e;
+      const double Pk = (double)(P >> (2 * (k + 1)));
+      bytes += 4 * Pk * 16 + Pk * 16 + 2 * Pk * 16 + 2.0 * Pk * cw[k] * e * 2;
     }
+    prof_begin(x);
+    FFV_TRY(check(launch_flow_pyramid((const float*)x.at(p.FM[2]), views, nv, g.Hp, g.Wp, fp, x.s), "flow pyramid"));
+    FFV_TRY(check(launch_ctx_warp(views, nv, cams, g.Hp, g.Wp, cw, fp, dst, lv_ld, dt_, x.s), "ctx_warp"));
+    prof_end(x, "pixel", nv * bytes);
   }
 
   // context-aware U-Net

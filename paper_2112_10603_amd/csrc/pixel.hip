@@ -156,12 +156,12 @@ __device__ inline void view_fastest_order(long& bx, int& v) {
 // time (these passes wait on latency more than on bytes); the stage
 // transition, whose record writes dominate, runs 10 % slower with it and
 // keeps the launch order.
-__device__ inline long banded_block() {
-  const unsigned gx = gridDim.x, i = blockIdx.x;
+__device__ inline long banded(unsigned i, unsigned gx) {  // block i of gx
   // the blocks of this image with the same id mod 8 share an XCD
   const unsigned r = i & 7u, q = gx >> 3, rem = gx & 7u;
   return (long)(r * q + (r < rem ? r : rem) + (i >> 3));
 }
+__device__ inline long banded_block() { return banded(blockIdx.x, gridDim.x); }
 
 // Half-pixel-centre source coordinate for resampling n_in -> n_out.
 __device__ inline void hp_tap(int i, int n_in, int n_out, int& i0, int& i1, float& w) {
@@ -209,42 +209,70 @@ __device__ inline float4 sample4(const float* img, const Tap4& t) {
   return r;
 }
 
-// ---------------------------------------------------------------- ingest
-template <typename T>
-__global__ void ingest_k(const float* const* src, int H, int W, int Hp, int Wp, float* X4, T* Xa) {
-  const int cam = blockIdx.y;
-  const long P = (long)Hp * Wp;
-  const long p = (long)blockIdx.x * TPB + threadIdx.x;
-  if (p >= P) return;
-  const int y = (int)(p / Wp), x = (int)(p % Wp);
-  const int sy = min(y, H - 1), sx = min(x, W - 1);
-  const float* s = src[cam];
-  const long HW = (long)H * W;
-  const float r = s[(long)sy * W + sx], g = s[HW + (long)sy * W + sx], b = s[2 * HW + (long)sy * W + sx];
-  *reinterpret_cast<float4*>(X4 + (cam * P + p) * 4) = make_float4(r, g, b, 0.f);
-  const float xv[8] = {r, g, b, 0.f, 0.f, 0.f, 0.f, 0.f};
-  store_vals<T, 8>(Xa + (cam * P + p) * 8, xv);
+// ------------------------------------------- ingest and image pyramid
+// Camera blockIdx.y: the replicate-padded image (4 floats per pixel, and 8
+// activations), then its quarter- and half-size copies, each sampled from
+// the planar source with the same clamped coordinates: workgroups
+// [0, n0) ingest, [n0, n0 + n1) quarter size, the rest half size. One launch
+// for every camera's passes: at small sizes a launch costs more than its
+// work (two 270x481 cameras took six launches and about 55 us with the gaps
+// between them, now one and 6 us; two 720p cameras 58 -> 17 us).
+struct IngestArgs {
+  const float* const* src;
+  int H, W, Hp, Wp;
+  char* block;  // camera 0's block
+  long stride;  // bytes between camera blocks
+  size_t X4, Xa, L0, L1;
+  int n0, n1;
+};
+
+// Pixel (y, x) of the padded image.
+__device__ inline float4 padded_pixel(const float* s, int H, int W, int y, int x) {
+  const long HW = (long)H * W, o = (long)min(y, H - 1) * W + min(x, W - 1);
+  return make_float4(s[o], s[HW + o], s[2 * HW + o], 0.f);
 }
 
-// ----------------------------------------------------- 4-channel resample
-__global__ void resample4_k(const float* in, int Hi, int Wi, float* out, int Ho, int Wo) {
-  const int img = blockIdx.y;
-  const long p = (long)blockIdx.x * TPB + threadIdx.x;
-  if (p >= (long)Ho * Wo) return;
-  const int y = (int)(p / Wo), x = (int)(p % Wo);
+// Bilinear sample (y, x) of the padded image resampled to Ho x Wo.
+__device__ inline float4 resampled_pixel(const float* s, int H, int W, int Hp, int Wp, int Ho, int Wo, int y, int x) {
   int y0, y1, x0, x1;
   float by, ax;
-  hp_tap(y, Hi, Ho, y0, y1, by);
-  hp_tap(x, Wi, Wo, x0, x1, ax);
-  const float* b = in + (long)img * Hi * Wi * 4;
-  float4 a00 = ld4(b + 4L * (y0 * Wi + x0)), a01 = ld4(b + 4L * (y0 * Wi + x1));
-  float4 a10 = ld4(b + 4L * (y1 * Wi + x0)), a11 = ld4(b + 4L * (y1 * Wi + x1));
+  hp_tap(y, Hp, Ho, y0, y1, by);
+  hp_tap(x, Wp, Wo, x0, x1, ax);
+  const float4 a00 = padded_pixel(s, H, W, y0, x0), a01 = padded_pixel(s, H, W, y0, x1);
+  const float4 a10 = padded_pixel(s, H, W, y1, x0), a11 = padded_pixel(s, H, W, y1, x1);
   float4 r;
   r.x = (a00.x * (1.f - ax) + a01.x * ax) * (1.f - by) + (a10.x * (1.f - ax) + a11.x * ax) * by;
   r.y = (a00.y * (1.f - ax) + a01.y * ax) * (1.f - by) + (a10.y * (1.f - ax) + a11.y * ax) * by;
   r.z = (a00.z * (1.f - ax) + a01.z * ax) * (1.f - by) + (a10.z * (1.f - ax) + a11.z * ax) * by;
-  r.w = (a00.w * (1.f - ax) + a01.w * ax) * (1.f - by) + (a10.w * (1.f - ax) + a11.w * ax) * by;
-  *reinterpret_cast<float4*>(out + ((long)img * Ho * Wo + p) * 4) = r;
+  r.w = 0.f;
+  return r;
+}
+
+template <typename T>
+__global__ void ingest_k(IngestArgs a) {
+  const int cam = blockIdx.y;
+  const float* s = a.src[cam];
+  char* block = a.block + cam * a.stride;
+  int b = blockIdx.x;
+  if (b < a.n0) {
+    const long p = (long)b * TPB + threadIdx.x;
+    if (p >= (long)a.Hp * a.Wp) return;
+    const int y = (int)(p / a.Wp), x = (int)(p % a.Wp);
+    const float4 v = padded_pixel(s, a.H, a.W, y, x);
+    *reinterpret_cast<float4*>(block + a.X4 + p * 16) = v;
+    const float xv[8] = {v.x, v.y, v.z, 0.f, 0.f, 0.f, 0.f, 0.f};
+    store_vals<T, 8>(reinterpret_cast<T*>(block + a.Xa) + p * 8, xv);
+    return;
+  }
+  b -= a.n0;
+  const int sh = b < a.n1 ? 2 : 1;
+  if (sh == 1) b -= a.n1;
+  const int Ho = a.Hp >> sh, Wo = a.Wp >> sh;
+  const long p = (long)b * TPB + threadIdx.x;
+  if (p >= (long)Ho * Wo) return;
+  const int y = (int)(p / Wo), x = (int)(p % Wo);
+  *reinterpret_cast<float4*>(block + (sh == 2 ? a.L0 : a.L1) + p * 16) =
+      resampled_pixel(s, a.H, a.W, a.Hp, a.Wp, Ho, Wo, y, x);
 }
 
 // ------------------------------------------------------ stage-0 input
@@ -383,41 +411,95 @@ __global__ void blend_out_k(const float* I2, const ViewDesc* views, int Hp, int 
 }
 
 // -------------------------------------------- flow pyramid: F/2 of 2x2 mean
-__global__ void flow_down_k(const float* in, int in_ld, const ViewDesc* views, int k, int h, int w, float* out) {
-  const int img = blockIdx.y;
-  const long bx = banded_block();
-  const int ho = h / 2, wo = w / 2;  // slot strides: h x w in, ho x wo out
-  const long p = bx * TPB + threadIdx.x;
-  const ViewDesc d = views[img];
-  const int vw = d.wp >> k;  // this view's level-k width
-  const int vwo = vw >> 1;
-  if (p >= (long)((d.hp >> k) >> 1) * vwo) return;
-  const int y = (int)(p / vwo), x = (int)(p % vwo);
-  const float* b = in + (long)img * h * w * in_ld;
-  const float4 a = ld4(b + (long)in_ld * ((2 * y) * vw + 2 * x));
-  const float4 c = ld4(b + (long)in_ld * ((2 * y) * vw + 2 * x + 1));
-  const float4 e = ld4(b + (long)in_ld * ((2 * y + 1) * vw + 2 * x));
-  const float4 g = ld4(b + (long)in_ld * ((2 * y + 1) * vw + 2 * x + 1));
+__device__ inline float4 flow_mean(const float4& a, const float4& c, const float4& e, const float4& g) {
   float4 r;
   r.x = 0.5f * (0.5f * (0.5f * (a.x + c.x) + 0.5f * (e.x + g.x)));
   r.y = 0.5f * (0.5f * (0.5f * (a.y + c.y) + 0.5f * (e.y + g.y)));
   r.z = 0.5f * (0.5f * (0.5f * (a.z + c.z) + 0.5f * (e.z + g.z)));
   r.w = 0.5f * (0.5f * (0.5f * (a.w + c.w) + 0.5f * (e.w + g.w)));
-  *reinterpret_cast<float4*>(out + ((long)img * ho * wo + p) * 4) = r;
+  return r;
+}
+
+// All four levels of a view from the full-resolution flow: a workgroup takes
+// 128 x 32 full-resolution pixels (64 x 16 of level 1, in LDS, then 32 x 8,
+// 16 x 4 and 8 x 2), so the coarser levels cost no launch and no second
+// read (four launches of 4.6 us each at small sizes). Padded sizes are
+// multiples of 16, so no 2 x 2 block crosses a border.
+struct FlowArgs {
+  const float* FM;  // 8 floats per pixel
+  const ViewDesc* views;
+  int h, w;         // slot strides: the launch's padded size
+  float* F[4];
+};
+__global__ __launch_bounds__(TPB) void flow_pyramid_k(FlowArgs t) {
+  __shared__ float4 lv[2][64 * 16];
+  const int v = blockIdx.y;
+  const long bx = banded_block();
+  const ViewDesc d = t.views[v];
+  const int tiles_x = (d.wp + 127) / 128, tiles_y = (d.hp + 31) / 32;
+  if (bx >= (long)tiles_x * tiles_y) return;  // uniform over the block
+  const int by = (int)(bx / tiles_x);
+  const int y0 = by * 16, x0 = (int)(bx - (long)by * tiles_x) * 64;  // level-1 origin
+  int vh = d.hp >> 1, vw = d.wp >> 1;
+  const float* b = t.FM + (long)v * t.h * t.w * 8;
+  long slot = (long)t.h * t.w >> 2;
+  for (int i = threadIdx.x; i < 64 * 16; i += TPB) {
+    const int y = y0 + (i >> 6), x = x0 + (i & 63);
+    if (y >= vh || x >= vw) continue;
+    const float* q = b + 8L * ((2 * y) * d.wp + 2 * x);
+    const float4 r = flow_mean(ld4(q), ld4(q + 8), ld4(q + 8L * d.wp), ld4(q + 8L * d.wp + 8));
+    lv[0][i] = r;
+    *reinterpret_cast<float4*>(t.F[0] + (v * slot + (long)y * vw + x) * 4) = r;
+  }
+#pragma unroll
+  for (int k = 1; k < 4; ++k) {
+    __syncthreads();
+    vh >>= 1;
+    vw >>= 1;
+    slot >>= 2;
+    const int tw = 64 >> k, n = (64 * 16) >> (2 * k);
+    const float4* in = lv[(k - 1) & 1];
+    for (int i = threadIdx.x; i < n; i += TPB) {
+      const int yy = i / tw, xx = i - yy * tw;
+      const int y = (y0 >> k) + yy, x = (x0 >> k) + xx;
+      if (y >= vh || x >= vw) continue;
+      const int o = 2 * yy * 2 * tw + 2 * xx;
+      const float4 r = flow_mean(in[o], in[o + 1], in[o + 2 * tw], in[o + 2 * tw + 1]);
+      lv[k & 1][i] = r;
+      *reinterpret_cast<float4*>(t.F[k] + (v * slot + (long)y * vw + x) * 4) = r;
+    }
+  }
 }
 
 // ------------------------------------------------ context-feature warp
 // One thread per (pixel, 8-channel group); groups [0, C/8) warp the left
 // camera's features by F_l, groups [C/8, C/4) the right's by F_r.
+// The four levels are sections of one grid (level k owns the workgroups
+// first[k] .. first[k+1]-1), each in banded order over its own range.
+struct CtxWarpArgs {
+  const ViewDesc* views;
+  const CamDev* cams;
+  int h, w;  // the launch's padded full-resolution size (slot strides)
+  int C[4];
+  const float* flow[4];
+  void* dst[4];
+  int ld[4];
+  long img_stride[4];
+  int first[5];
+};
 template <typename T>
-__global__ void ctx_warp_k(const ViewDesc* views, const CamDev* cams, int level, int C,
-                           const float* flow, int h, int w, T* dst, int dst_ld, long dst_img_stride) {
+__global__ void ctx_warp_k(CtxWarpArgs t) {
+  int level = 0;
+#pragma unroll
+  for (int k = 1; k < 4; ++k)
+    if ((int)blockIdx.x >= t.first[k]) level = k;
   const int v = blockIdx.y;
-  const long bx = banded_block();
+  const long bx = banded(blockIdx.x - t.first[level], t.first[level + 1] - t.first[level]);
+  const int C = t.C[level];
   const int G = C / 4;  // groups for both sides
-  const long P = (long)h * w;  // slot stride
+  const long P = (long)(t.h >> (level + 1)) * (t.w >> (level + 1));  // slot stride
   const long id = bx * TPB + threadIdx.x;
-  const ViewDesc d = views[v];
+  const ViewDesc d = t.views[v];
   const int vh = d.hp >> (level + 1), vw = d.wp >> (level + 1);  // this view's level size
   if (id >= (long)vh * vw * G) return;
   const long p = id / G;
@@ -425,14 +507,14 @@ __global__ void ctx_warp_k(const ViewDesc* views, const CamDev* cams, int level,
   const bool right = g >= G / 2;
   const int c0 = (right ? g - G / 2 : g) * 8;
   const int y = (int)(p / vw), x = (int)(p % vw);
-  const float4 F = ld4(flow + ((long)v * P + p) * 4);
-  const Tap4 t = right ? warp_taps(x, y, F.z, F.w, vw, vh) : warp_taps(x, y, F.x, F.y, vw, vh);
-  const T* src = reinterpret_cast<const T*>(cams[right ? d.cam_r : d.cam_l].ctx[level]) + c0;
+  const float4 F = ld4(t.flow[level] + ((long)v * P + p) * 4);
+  const Tap4 tp = right ? warp_taps(x, y, F.z, F.w, vw, vh) : warp_taps(x, y, F.x, F.y, vw, vh);
+  const T* src = reinterpret_cast<const T*>(t.cams[right ? d.cam_r : d.cam_l].ctx[level]) + c0;
   float acc[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-  const int offs[4] = {t.o00, t.o01, t.o10, t.o11};
-  const float ws[4] = {t.w00, t.w01, t.w10, t.w11};
+  const int offs[4] = {tp.o00, tp.o01, tp.o10, tp.o11};
+  const float ws[4] = {tp.w00, tp.w01, tp.w10, tp.w11};
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     float a[8];
@@ -440,7 +522,9 @@ __global__ void ctx_warp_k(const ViewDesc* views, const CamDev* cams, int level,
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] += ws[q] * a[i];
   }
-  store_vals<T, 8>(dst + (long)v * dst_img_stride + p * dst_ld + (right ? C : 0) + c0, acc);
+  store_vals<T, 8>(reinterpret_cast<T*>(t.dst[level]) + (long)v * t.img_stride[level] + p * t.ld[level] +
+                       (right ? C : 0) + c0,
+                   acc);
 }
 
 // ----------------------------------------------------------- output head
@@ -533,7 +617,8 @@ __global__ void head_k(const T* u4, int ld, const float* wgt, const float* bias,
 // load), and ends with that pixel's three pre-activations in its first
 // accumulators (lanes 0-31). The weights are rounded to bf16 (as every other
 // bf16 layer's) and laid out once per block as MFMA fragments in LDS; a
-// block covers HEAD_GROUPS groups per wave to amortise that.
+// block covers up to HEAD_GROUPS groups per wave to amortise that, fewer
+// where the launch would leave compute units without a block.
 constexpr int HEAD_GROUPS = 32;
 // threads per block of the MFMA head: eight waves share one weight table
 // (measured 6 % faster than four at 1080p x 112 views)
@@ -542,7 +627,8 @@ constexpr int HEAD_TPB = 512;
 template <int C>
 __global__ __launch_bounds__(HEAD_TPB) void head_mfma_k(const bf16* u4, int ld, const float* wgt,
                                                    const float* bias, const float* I2,
-                                                   const ViewDesc* views, int Hp, int Wp, int H, int W) {
+                                                   const ViewDesc* views, int Hp, int Wp, int H, int W,
+                                                   int groups) {
   constexpr int NC = C / 16;  // MFMAs per tap
   constexpr int WAVES = HEAD_TPB / 64;
   __shared__ uint4 wtab[9 * NC * 64];  // [tap][j][lane] weight fragments
@@ -575,9 +661,9 @@ __global__ __launch_bounds__(HEAD_TPB) void head_mfma_k(const bf16* u4, int ld, 
   // iteration halve the round trips but need 132 registers, three waves
   // per SIMD; one group keeps more waves resident and measured 16 % faster
   // at 1080p x 112 views.)
-  for (int g = 0; g < HEAD_GROUPS; ++g) {
-    if ((bx * HEAD_GROUPS + g) * WAVES * 32 >= HW) break;  // uniform over the block
-    const long p = ((bx * HEAD_GROUPS + g) * WAVES + wave) * 32 + lrow;
+  for (int g = 0; g < groups; ++g) {
+    if ((bx * groups + g) * WAVES * 32 >= HW) break;  // uniform over the block
+    const long p = ((bx * groups + g) * WAVES + wave) * 32 + lrow;
     const bool pin = p < HW;
     const int y = pin ? (int)(p / W) : 0;
     const int x = pin ? (int)(p % W) : 0;
@@ -642,23 +728,14 @@ inline dim3 grid1(long n, int y) { return dim3((unsigned)((n + TPB - 1) / TPB), 
       hipLaunchKernelGGL(KERNEL<bf16>, __VA_ARGS__);                       \
   } while (0)
 
-hipError_t launch_ingest(const float* const* src, int n_cam, int H, int W, int Hp, int Wp, float* X4,
-                         void* Xa, DType dt, hipStream_t s) {
+hipError_t launch_ingest(const float* const* src, int n_cam, int H, int W, int Hp, int Wp, char* block, long stride,
+                         size_t X4, size_t Xa, size_t L0, size_t L1, DType dt, hipStream_t s) {
   if (n_cam <= 0) return hipSuccess;
-  if (dt == DType::F32)
-    hipLaunchKernelGGL(ingest_k<float>, grid1((long)Hp * Wp, n_cam), dim3(TPB), 0, s, src, H, W, Hp,
-                       Wp, X4, (float*)Xa);
-  else
-    hipLaunchKernelGGL(ingest_k<bf16>, grid1((long)Hp * Wp, n_cam), dim3(TPB), 0, s, src, H, W, Hp,
-                       Wp, X4, (bf16*)Xa);
-  return hipGetLastError();
-}
-
-hipError_t launch_resample4(const float* in, int n_img, int Hi, int Wi, float* out, int Ho, int Wo,
-                            hipStream_t s) {
-  if (n_img <= 0) return hipSuccess;
-  hipLaunchKernelGGL(resample4_k, grid1((long)Ho * Wo, n_img), dim3(TPB), 0, s, in, Hi, Wi, out, Ho,
-                     Wo);
+  const long P = (long)Hp * Wp;
+  auto blocks = [](long n) { return (int)((n + TPB - 1) / TPB); };
+  IngestArgs a{src, H, W, Hp, Wp, block, stride, X4, Xa, L0, L1, blocks(P), blocks(P / 16)};
+  const dim3 grid((unsigned)(a.n0 + a.n1 + blocks(P / 4)), (unsigned)n_cam);
+  FFV_DISPATCH(dt, ingest_k, grid, dim3(TPB), 0, s, a);
   return hipGetLastError();
 }
 
@@ -702,29 +779,40 @@ hipError_t launch_final(const ViewDesc* views, int n_views, const CamDev* cams, 
   return hipGetLastError();
 }
 
-hipError_t launch_flow_down(const float* in, int in_ld, const ViewDesc* views, int n_img, int k, int h, int w,
-                            float* out, hipStream_t s) {
+hipError_t launch_flow_pyramid(const float* FM, const ViewDesc* views, int n_img, int h, int w, float* const F[4],
+                               hipStream_t s) {
   if (n_img <= 0) return hipSuccess;
-  hipLaunchKernelGGL(flow_down_k, grid1((long)(h / 2) * (w / 2), n_img), dim3(TPB), 0, s, in, in_ld, views, k,
-                     h, w, out);
+  if (h % 16 != 0 || w % 16 != 0) return hipErrorInvalidValue;
+  const FlowArgs a{FM, views, h, w, {F[0], F[1], F[2], F[3]}};
+  // (a view of a mixed batch is at most h x w, so it has no more tiles)
+  const dim3 grid((unsigned)(((w + 127) / 128) * (long)((h + 31) / 32)), (unsigned)n_img);
+  hipLaunchKernelGGL(flow_pyramid_k, grid, dim3(TPB), 0, s, a);
   return hipGetLastError();
 }
 
-hipError_t launch_ctx_warp(const ViewDesc* views, int n_views, const CamDev* cams, int level, int C,
-                           const float* flow, int h, int w, void* dst, int dst_ld,
-                           long dst_img_stride, DType dt, hipStream_t s) {
+hipError_t launch_ctx_warp(const ViewDesc* views, int n_views, const CamDev* cams, int h, int w, const int C[4],
+                           float* const flow[4], void* const dst[4], const int ld[4], DType dt, hipStream_t s) {
   if (n_views <= 0) return hipSuccess;
-  // 8-channel groups as 16-byte loads and stores
-  if (C % 8 != 0 || dst_ld % 8 != 0 || dst_img_stride % 8 != 0 ||
-      reinterpret_cast<uintptr_t>(dst) % 16 != 0)
-    return hipErrorInvalidValue;
-  const long n = (long)h * w * (C / 4);
-  if (dt == DType::F32)
-    hipLaunchKernelGGL(ctx_warp_k<float>, grid1(n, n_views), dim3(TPB), 0, s, views, cams, level, C,
-                       flow, h, w, (float*)dst, dst_ld, dst_img_stride);
-  else
-    hipLaunchKernelGGL(ctx_warp_k<bf16>, grid1(n, n_views), dim3(TPB), 0, s, views, cams, level, C,
-                       flow, h, w, (bf16*)dst, dst_ld, dst_img_stride);
+  CtxWarpArgs a{};
+  a.views = views;
+  a.cams = cams;
+  a.h = h;
+  a.w = w;
+  for (int k = 0; k < 4; ++k) {
+    const long P = (long)(h >> (k + 1)) * (w >> (k + 1));
+    // 8-channel groups as 16-byte loads and stores
+    if (C[k] % 8 != 0 || ld[k] % 8 != 0 || reinterpret_cast<uintptr_t>(dst[k]) % 16 != 0) return hipErrorInvalidValue;
+    a.C[k] = C[k];
+    a.flow[k] = flow[k];
+    a.dst[k] = dst[k];
+    a.ld[k] = ld[k];
+    a.img_stride[k] = P * ld[k];
+    const long n = (long)a.first[k] + (P * (C[k] / 4) + TPB - 1) / TPB;
+    if (n > 0x7fffffffL) return hipErrorInvalidValue;
+    a.first[k + 1] = (int)n;
+  }
+  const dim3 grid((unsigned)a.first[4], (unsigned)n_views);
+  FFV_DISPATCH(dt, ctx_warp_k, grid, dim3(TPB), 0, s, a);
   return hipGetLastError();
 }
 
@@ -734,14 +822,21 @@ hipError_t launch_head(const void* u4, int ld, int C, const float* w, const floa
   if (n_img <= 0) return hipSuccess;
   if (C <= 0 || C > 64 || C % 8 != 0 || C > ld || ld % 8 != 0) return hipErrorInvalidValue;
   if (dt == DType::BF16 && (C == 16 || C == 32)) {
-    const long per_block = (long)HEAD_GROUPS * (HEAD_TPB / 64) * 32;  // groups of 32 pixels per wave
+    // At least two blocks per compute unit (as many as fit at a time) before
+    // a block's weight table is spread over more groups: one 720p view 63 us
+    // with 32 groups (113 blocks), 29 with 4 (900 blocks) and with 2; one
+    // 270x481 view 59 -> 7 us.
+    int groups = HEAD_GROUPS;
+    const long units = ((long)H * W + (HEAD_TPB / 64) * 32 - 1) / ((HEAD_TPB / 64) * 32) * n_img;
+    while (groups > 1 && units / groups < 512) groups >>= 1;
+    const long per_block = (long)groups * (HEAD_TPB / 64) * 32;
     const dim3 g((unsigned)(((long)H * W + per_block - 1) / per_block), (unsigned)n_img);
     if (C == 16)
       hipLaunchKernelGGL(head_mfma_k<16>, g, dim3(HEAD_TPB), 0, s, (const bf16*)u4, ld, w, b, I2, views, Hp, Wp,
-                         H, W);
+                         H, W, groups);
     else
       hipLaunchKernelGGL(head_mfma_k<32>, g, dim3(HEAD_TPB), 0, s, (const bf16*)u4, ld, w, b, I2, views, Hp, Wp,
-                         H, W);
+                         H, W, groups);
     return hipGetLastError();
   }
   const dim3 grid = grid1((long)H * W, n_img);
