@@ -657,6 +657,62 @@ int halo_default_width(DType dt, const ConvArgs& a0) {
   return best;
 }
 
+// Tile and pixel block width of a launch without a tuning entry (and not of
+// the direct-weight kernel). The figures are us per launch, one MI355X.
+void default_tile(DType kdt, const ConvArgs& a, ConvTile narrowest, ConvTile* tile, int* tile_w) {
+  const int rows = a.n_rows;
+  *tile = narrowest;  // the narrowest generic tile that holds the layer
+  *tile_w = conv_tile_width(a.Ho, a.Wo);
+  const bool matrix16 = kdt != DType::F32;
+  const int hw = matrix16 ? halo_default_width(kdt, a) : 0;  // 0: no halo tile runs it
+  auto m_tiles = [&](int tw) {
+    const int th = 256 / tw;
+    return (long)a.n_img * ((a.Ho + th - 1) / th) * ((a.Wo + tw - 1) / tw);
+  };
+  auto use = [&](ConvTile t, int tw) {
+    *tile = t;
+    *tile_w = tw;
+  };
+  // few output channels over a stride-1 3x3 neighbourhood: the persistent
+  // kernel with resident weights where they fit, else the halo kernel
+  if (rows <= 64 && conv_resident_ok(kdt, a, rows <= 32 ? 32 : 64)) return use(rows <= 32 ? ConvTile::R32 : ConvTile::R64, 16);
+  if (rows <= 32 && conv_halo_ok(kdt, a)) return use(ConvTile::H32, 16);
+  if (a.transposed == 1 && hw > 0) {
+    // per-phase transposed convs: two phases (at most 128 outputs) or four
+    // (at most 64) per 256-column halo tile, once those fill the chip; fp8
+    // launches of at most one round of 128-column tiles take those (256 ->
+    // 128 at 90x160: 16.9 against 22.4; at 180x320 57.6 against 46.6, and in
+    // bf16 95 against 76, the generic tile 105)
+    if (rows <= 64 && m_tiles(hw) >= 200) return use(ConvTile::Q256, hw);
+    if (rows > 64 && rows <= 128)
+      return use(kdt == DType::FP8 && 4 * m_tiles(hw) <= 256 ? ConvTile::H128 : ConvTile::P256, hw);
+  }
+  if (!a.transposed && hw > 0 && rows > 64) {
+    // 3x3 stride-1 convs: with more than 128 outputs (the 256-channel
+    // chains) the two-group halo tile; 128-column halo tiles for at most 128
+    // outputs, and in fp8 for launches of one round of them (256 -> 256 at
+    // 90x160: 22.7 against 29.9; at 135x240, 270 workgroups, 45.8 against 33.9)
+    if (rows <= 128 || (kdt == DType::FP8 && m_tiles(hw) * ((rows + 127) / 128) <= 256))
+      return use(ConvTile::H128, hw);
+    return use(ConvTile::P256, hw);
+  }
+  if (!a.transposed && matrix16 && !a.out_f32 && rows <= 128) {
+    // convs over a few input channels (8 to 32): the persistent kernel with
+    // resident weights, narrowest N tile that holds the layer
+    const int bn = rows <= 32 ? 32 : (rows <= 64 ? 64 : 128);
+    if (conv_resident_s2_ok(kdt, a, bn))
+      return use(bn == 32 ? ConvTile::S32 : (bn == 64 ? ConvTile::S64 : ConvTile::S128), 16);
+  }
+  // wide layers on small grids: narrower tiles while their workgroups fit one
+  // round (fp8 128 -> 256, stride 2, 90x160 outputs: 64 columns 14.5, 128 17.4,
+  // 256 23.7; 180x320: 58, 38, 28)
+  if (matrix16 && rows > 64) {
+    const long t = m_tiles(*tile_w) * (a.transposed == 1 ? 4 : 1);
+    if (t * ((rows + 63) / 64) <= 256) return use(ConvTile::N64, *tile_w);
+    if (t * ((rows + 127) / 128) <= 256) return use(ConvTile::N128, *tile_w);
+  }
+}
+
 }  // namespace
 
 Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long in_img_stride,
@@ -702,45 +758,23 @@ Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long 
   a.accumulate = accumulate ? 1 : 0;
   a.taps = L.mode == 1 ? 4 : 9;
   a.zero = zero_;
-  a.tile_w = conv_tile_width(a.Ho, a.Wo);
-  ConvTile tile = L.tile;
   const DType kdt = in_fp8 ? DType::FP8 : dt_;
-  // few output channels over a stride-1 3x3 neighbourhood: the persistent
-  // kernel with resident weights where they fit, else the halo kernel
-  if (L.rows <= 64 && conv_resident_ok(kdt, a, L.rows <= 32 ? 32 : 64)) {
-    tile = L.rows <= 32 ? ConvTile::R32 : ConvTile::R64;
-    a.tile_w = 16;
-  } else if (L.rows <= 32 && conv_halo_ok(kdt, a)) {
-    tile = ConvTile::H32;
-    a.tile_w = 16;
-  } else if (!L.transposed && kdt != DType::F32 && L.rows > 128 && halo_default_width(kdt, a) > 0) {
-    // 3x3 stride-1 convs with more than 128 outputs (the 256-channel chains):
-    // the two-group halo tile, the fastest tile for them when tuned, at the
-    // least padded block width it accepts
-    tile = ConvTile::P256;
-    a.tile_w = halo_default_width(kdt, a);
-  } else if (!L.transposed && !out_f32 && L.rows <= 128) {
-    // convs over a few input channels (8 to 32): the persistent kernel with
-    // resident weights, narrowest N tile that holds the layer
-    const int bn = L.rows <= 32 ? 32 : (L.rows <= 64 ? 64 : 128);
-    if (conv_resident_s2_ok(kdt, a, bn)) {
-      tile = bn == 32 ? ConvTile::S32 : (bn == 64 ? ConvTile::S64 : ConvTile::S128);
-      a.tile_w = 16;
-    }
-  }
+  ConvTile tile = L.tile;
   // small grids, and every fp32 layer: the direct-weight kernel (whatever the
   // tuning table says: the table chooses among the other tiles)
   int direct_w = 0;
   const DirectTile direct = conv_direct_tile(kdt, a, &direct_w);
-  if (!tuned_.empty() || recording_) {
-    const TuneKey key{L.name, in_fp8 ? 1 : 0, a.Ho, a.Wo, n_img};
-    auto it = tuned_.find(key);
+  auto pick = [&](const ConvArgs& c, ConvTile* t, int* tw) {  // the rule's tile, or the table's
+    default_tile(kdt, c, L.tile, t, tw);
+    auto it = tuned_.find(TuneKey{L.name, in_fp8 ? 1 : 0, c.Ho, c.Wo, c.n_img});
     if (it != tuned_.end()) {
-      tile = it->second.tile;
-      a.tile_w = it->second.tile_w;
+      *t = it->second.tile;
+      *tw = it->second.tile_w;
     }
-    if (recording_) recs_.push_back(TuneRec{key, a, kdt, direct != DirectTile::None});
-  }
+  };
+  pick(a, &tile, &a.tile_w);
+  if (recording_)
+    recs_.push_back(TuneRec{TuneKey{L.name, in_fp8 ? 1 : 0, a.Ho, a.Wo, n_img}, a, kdt, direct != DirectTile::None});
   if (in_ld < L.cin_pad || in_ld % (in_fp8 ? 16 : 8) != 0) return Status::err(-4, "conv input stride");
   if ((in_fp8 && !L.w8_dev) || (out_fp8 && !L.out_scale)) return Status::err(-7, "fp8 layer not quantised");
   const double flops = 2.0 * n_img * (double)a.Hout * a.Wout * L.cout * L.cin *
@@ -760,14 +794,6 @@ Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long 
     int n_total = 0;
     for (int j = 0; j < x.n_groups; ++j) n_total += x.groups[j].n;
     if (n_total != n_img || x.n_groups > ConvGroup::kMax) return Status::err(-4, "grouped conv: groups");
-    // tiles without a grouped form (the persistent kernels, the one-group
-    // halo tiles): the generic tile of the same N width
-    ConvTile gt = tile;
-    if (!conv_tile_groupable(gt)) {
-      const int bn = conv_tile_bn(gt);
-      gt = bn == 32 ? ConvTile::N32 : (bn == 64 ? ConvTile::N64 : (bn == 128 ? ConvTile::N128 : ConvTile::N256));
-    }
-    bool halo_tile = gt == ConvTile::P256;
     const size_t in_e = in_fp8 ? 1 : dtype_size(dt_);
     const size_t out_e = out_f32 ? 4 : (out_fp8 ? 1 : dtype_size(dt_));
     ConvArgs g[ConvGroup::kMax];
@@ -792,34 +818,37 @@ Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long 
       }
       b.in = static_cast<const char*>(in) + (size_t)vg.first * in_img_stride * in_e;
       b.out = static_cast<char*>(out) + (size_t)vg.first * out_img_stride * out_e;
-      b.tile_w = halo_tile ? halo_default_width(kdt, b) : conv_tile_width(b.Ho, b.Wo);
-      if (b.tile_w == 0) {
-        // the halo tiles cannot take this group: the generic tile of the same
-        // N width for every group (restart; the generic tile takes any width)
-        gt = conv_tile_bn(gt) == 256 ? ConvTile::N256 : ConvTile::N128;
-        halo_tile = false;
-        j = -1;
-        gflops = 0.0;
-        continue;
-      }
       gflops += 2.0 * vg.n * (double)b.Hout * b.Wout * L.cout * L.cin * (L.transposed ? 4.0 : 9.0);
     }
-    // groups the direct kernel takes are launched one by one, the others together
+    // Each group runs the tile it would have alone: the direct and the
+    // persistent kernels group by group, tiles with a grouped form together
+    // with the other groups of the same tile.
     prof_begin(x);
     Status st = Status::ok();
-    int rest = 0;
+    ConvTile gt[ConvGroup::kMax];
+    bool done[ConvGroup::kMax] = {};
     for (int j = 0; j < x.n_groups && st.good(); ++j) {
-      ConvArgs b = g[j];
       int tw = 0;
-      const DirectTile d = conv_direct_tile(kdt, b, &tw);
-      if (d == DirectTile::None) {
-        g[rest++] = g[j];
-        continue;
-      }
-      b.tile_w = tw;
-      st = check(launch_conv_direct(kdt, d, b, x.s), L.name.c_str());
+      const DirectTile d = conv_direct_tile(kdt, g[j], &tw);
+      pick(g[j], &gt[j], &g[j].tile_w);
+      if (d != DirectTile::None) g[j].tile_w = tw;
+      done[j] = d != DirectTile::None || !conv_tile_groupable(gt[j]);
+      if (d != DirectTile::None)
+        st = check(launch_conv_direct(kdt, d, g[j], x.s), L.name.c_str());
+      else if (done[j])
+        st = check(launch_conv(kdt, gt[j], g[j], x.s), L.name.c_str());
     }
-    if (st.good() && rest > 0) st = check(launch_conv_grouped(kdt, gt, g, rest, x.s), L.name.c_str());
+    for (int j = 0; j < x.n_groups && st.good(); ++j) {
+      if (done[j]) continue;
+      ConvArgs same[ConvGroup::kMax];
+      int n_same = 0;
+      for (int k2 = j; k2 < x.n_groups; ++k2)
+        if (!done[k2] && gt[k2] == gt[j]) {
+          same[n_same++] = g[k2];
+          done[k2] = true;
+        }
+      st = check(launch_conv_grouped(kdt, gt[j], same, n_same, x.s), L.name.c_str());
+    }
     prof_end(x, cls, gflops);
     return st;
   }
