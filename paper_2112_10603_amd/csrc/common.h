@@ -115,13 +115,17 @@ bool conv_resident_ok(DType dt, const ConvArgs& a, int bn);
 bool conv_resident_s2_ok(DType dt, const ConvArgs& a, int bn);
 
 // Tiles (pixels x GEMM columns) of the kernel whose weights go straight into
-// registers (conv_direct.h). Every tile computes the same values.
-enum class DirectTile : int { None = 0, M64N64, M64N128, M128N32, M128N64, M128N128, M128N256, M256N128 };
+// registers (conv_direct.h). Every tile computes the same values, but for the
+// last four: they add the same sums in eight parts, by eight waves of a
+// workgroup (K) or one part after the other (F), and agree among themselves.
+enum class DirectTile : int {
+  None = 0, M64N64, M64N128, M128N32, M128N64, M128N128, M128N256, M256N128, M32N32K, M64N64F, M64N128F, M128N32F
+};
 // The direct tile for a launch and its pixel block width (*tile_w), or None
 // when the tiles of ConvTile serve it better or the kernel cannot run it.
 // a.wfrag only needs to be non-null. fp32 launches take a direct tile
-// wherever the kernel can run them, whatever the number of images, so that a
-// view does not depend on its batch.
+// wherever the kernel can run them, and the sums of a tile depend on the layer
+// and the image size alone, so that a view does not depend on its batch.
 DirectTile conv_direct_tile(DType dt, const ConvArgs& a, int* tile_w);
 hipError_t launch_conv_direct(DType dt, DirectTile tile, const ConvArgs& a, hipStream_t s);
 hipError_t launch_direct_f32(DirectTile tile, const ConvArgs& a, hipStream_t s);

@@ -82,9 +82,13 @@ template <typename T>
 bool direct_fits_t(const ConvArgs& a, DirectTile tile) {
   using namespace convk;
   switch (tile) {
+    case DirectTile::M64N64F:
     case DirectTile::M64N64: return direct_plan<T, 256, 64>(a, 64).nbuf > 0;
+    case DirectTile::M64N128F:
     case DirectTile::M64N128: return direct_plan<T, 256, 128>(a, 64).nbuf > 0;
+    case DirectTile::M128N32F:
     case DirectTile::M128N32: return direct_plan<T, 256, 32>(a, 128).nbuf > 0;
+    case DirectTile::M32N32K: return direct_plan<T, 64 * kDirectParts, 32>(a, 32, true).nbuf > 0;
     case DirectTile::M128N64: return direct_plan<T, 256, 64>(a, 128).nbuf > 0;
     case DirectTile::M128N128: return direct_plan<T, 256, 128>(a, 128).nbuf > 0;
     case DirectTile::M128N256: return direct_plan<T, 512, 256>(a, 128).nbuf > 0;
@@ -156,9 +160,37 @@ DirectTile conv_direct_tile(DType dt, const ConvArgs& a0, int* tile_w) {
       m128n32{DirectTile::M128N32, 128, 32}, m128n64{DirectTile::M128N64, 128, 64},
       m128n128{DirectTile::M128N128, 128, 128}, m128n256{DirectTile::M128N256, 128, 256},
       m256n128{DirectTile::M256N128, 256, 128};
+  const Cand m32n32k{DirectTile::M32N32K, 32, 32}, m64n64f{DirectTile::M64N64F, 64, 64},
+      m64n128f{DirectTile::M64N128F, 64, 128}, m128n32f{DirectTile::M128N32F, 128, 32};
   int tw = 0;
   long n;
   if (dt == DType::F32) {
+    // Small images, several channel slices: a tile's K rounds shared by eight
+    // waves (the chain of one wave's MFMAs is the launch's time). us of 32x32
+    // tiles, K shared / best other tile: 256 -> 256 at 16x16 10.5 / 26, 32x32
+    // (256 workgroups) 12 / 27, 32x64 (512) 23 / 30, 45x80 (920) 43 / 33;
+    // stride 2, 128 -> 256, 16x16 8 / 17; transposed 256 -> 128 at 16x16 8 /
+    // 15.5, 32x32 (512) 15 / 17; 128 -> 5 at 64x64 9.5 / 18. So up to 512
+    // workgroups. Whether the sum is in parts goes by one image; a launch of
+    // more images takes the tiles that add the same parts in turn (3 to 10 %
+    // slower than those that need not).
+    if (a0.cin_pad > 32 && (a0.transposed != 2 || a0.cout <= 32)) {
+      n = blocks(m32n32k, &tw);
+      const long n1 = a0.n_img > 0 ? n / a0.n_img : 0;
+      if (n1 > 0 && n1 <= 512) {
+        if (n > 512) {
+          int tf = 0;
+          const long nf = rows > 64 ? blocks(m64n64f, &tf) : 0;
+          for (const Cand& c : {rows <= 32 ? m128n32f : rows > 64 && nf > 256 ? m64n128f : m64n64f, m64n64f})
+            if (blocks(c, &tf) > 0) {
+              *tile_w = tf;
+              return c.tile;
+            }
+        }
+        *tile_w = tw;
+        return m32n32k.tile;
+      }
+    }
     // One workgroup per compute unit: the smallest tile whose workgroups fit
     // the 256 units in one round, else the largest (its weight fragments
     // feed the most MFMAs). 256 -> 256, 3x3, us of 64x64 / 64x128 / 128x128

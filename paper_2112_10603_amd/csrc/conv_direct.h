@@ -31,7 +31,10 @@
 // What bounds it. Small grids: the chain of a workgroup's K rounds (144 for
 // 256 channels), an MFMA of 32 cycles each plus what of the LDS read is not
 // hidden; 256 -> 256 at 45x80 takes 10 us where the tiles of conv_kernel.h
-// take 15 to 65 (a barrier and a full load latency per K step). fp32: the
+// take 15 to 65 (a barrier and a full load latency per K step). An fp32 round
+// is five dependent MFMAs and the splitting of its activations, so small
+// fp32 images share a tile's K sum among eight waves (KS): 256 -> 256 at
+// 32x32 27 -> 12 us, at 8x8 26 -> 10. Larger fp32 launches: the
 // matrix cores and power; 256 -> 256 at 270x480 takes 823 us = 186 TFLOP/s
 // (1255 us on fp32 MFMA), MFMA pipes 68 % busy at 1.69 GHz, the rest being
 // weight-load waits (14 %), the first slice of each workgroup and the
@@ -83,13 +86,17 @@ constexpr int direct_loads(int bm, int st, int nt) {
 
 constexpr int kDirectLdsVecs = 160 * 1024 / 16;
 
+// Parts of a K sum whose slices are shared out (KS or FOLD below), each a run
+// of per slices; fewer slices than parts make one part each.
+constexpr int kDirectParts = 8;
+
 // LDS buffers of a launch: vecs 16-byte chunks each (whole loads of every
 // thread), nbuf of them; 0 when not even the slices needed at once fit.
 struct DirectPlan {
-  int loads, vecs, nbuf, slices;
+  int loads, vecs, nbuf, slices, per;
 };
 template <typename T, int NT, int BN>
-inline DirectPlan direct_plan(const ConvArgs& a, int bm) {
+inline DirectPlan direct_plan(const ConvArgs& a, int bm, bool all = false) {
   DirectPlan p{};
   const DirectHalo h(bm / a.tile_w, a.tile_w, a.stride);
   p.loads = (h.hh * h.hw * 8 + NT - 1) / NT;
@@ -97,7 +104,8 @@ inline DirectPlan direct_plan(const ConvArgs& a, int bm) {
   p.slices = (a.cin_pad * (int)sizeof(T) + 127) / 128;
   const int fit = (kDirectLdsVecs - 3 * BN * 4 / 16) / p.vecs;
   p.nbuf = fit < p.slices ? fit : p.slices;
-  if (p.nbuf < 2 && p.nbuf < p.slices) p.nbuf = 0;
+  if ((p.nbuf < 2 || all) && p.nbuf < p.slices) p.nbuf = 0;
+  p.per = (p.slices + kDirectParts - 1) / kDirectParts;
   return p;
 }
 
@@ -114,11 +122,15 @@ __device__ inline uint32_t split_stage(float& x0, float& x1, int stage) {
 
 // D, PA: rounds that the weights and the halo reads run ahead of the MFMAs.
 // ST: stride of a 3x3 conv (1 or 2); transposed convs (4 taps per phase, or
-// 9 phase-merged) use ST 1. LA: most halo loads per thread and slice.
-template <typename T, int TAPS, int ST, int FM, int FN, int WM, int WN, int D, int PA>
-__global__ __launch_bounds__(64 * WM * WN) void conv_direct(ConvArgs a, DirectPlan pl) {
+// 9 phase-merged) use ST 1. KS: waves that share the K sum, one part each,
+// added in order through LDS at the end. FOLD: the same parts one after the
+// other in every wave: the same values as KS = kDirectParts.
+template <typename T, int TAPS, int ST, int FM, int FN, int WM, int WN, int D, int PA, int KS = 1, bool FOLD = false>
+__global__ __launch_bounds__(64 * WM * WN * KS) void conv_direct(ConvArgs a, DirectPlan pl) {
   using X = DirectType<T>;
-  constexpr int NT = 64 * WM * WN, BM = 32 * FM * WM, BN = 32 * FN * WN;
+  constexpr int NT = 64 * WM * WN * KS, BM = 32 * FM * WM, BN = 32 * FN * WN;
+  static_assert(KS == 1 || (KS == kDirectParts && sizeof(T) == 4 && FM * FN * WM * WN == 1 && !FOLD), "one tile, shared K");
+  static_assert(!FOLD || sizeof(T) == 4, "fp32 only");
   constexpr int R = X::R, LOADS = X::LOADS, U = TAPS * R;
   constexpr int VEC = 16 / (int)sizeof(T), BK = 128 / (int)sizeof(T);
   constexpr int LA = direct_loads(BM, ST, NT);
@@ -128,7 +140,9 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_direct(ConvArgs a, DirectPl
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
+  const int kw = KS > 1 ? wave : 0;
+  const int wm = KS > 1 ? 0 : wave / WN, wn = KS > 1 ? 0 : wave % WN;
+  const int s0 = KS > 1 ? min(kw * pl.per, pl.slices) : 0, s1 = KS > 1 ? min(s0 + pl.per, pl.slices) : pl.slices;
   const int lrow = lane & 31, lhalf = lane >> 5;
   const bool merged = a.transposed == 2;
 
@@ -215,13 +229,14 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_direct(ConvArgs a, DirectPl
   const uint32_t lane16 = lane * 16;
   gptr_t bp[FN];
 #pragma unroll
-  for (int j = 0; j < FN; ++j) bp[j] = (gptr_t)a.wfrag + ((long)phase * n32 + n0 / 32 + wn * FN + j) * stream;
+  for (int j = 0; j < FN; ++j) bp[j] = (gptr_t)a.wfrag + ((long)phase * n32 + n0 / 32 + wn * FN + j) * stream + (long)s0 * (U * LOADS * 1024);
   auto weight = [&](int j, int k) {  // fragment k of stream j from its current place
     return __builtin_bit_cast(uint4, *(gvec_t)(bp[j] + k * 1024 + lane16));
   };
 
   f32x16 acc[FM][FN];
   f32x16 acc2[F32 ? FM : 1][F32 ? FN : 1];
+  f32x16 tot[FOLD ? FM : 1][FOLD ? FN : 1];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -230,6 +245,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_direct(ConvArgs a, DirectPl
       for (int e = 0; e < 16; ++e) {
         acc[i][j][e] = 0.f;
         if constexpr (F32) acc2[i][j][e] = 0.f;
+        if constexpr (FOLD) tot[i][j][e] = 0.f;
       }
 
   for (int s = 0; s < pl.nbuf; ++s) issue(s, s);
@@ -249,8 +265,8 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_direct(ConvArgs a, DirectPl
   __syncthreads();
 
   const char* lds = reinterpret_cast<const char*>(dsm);
-  int buf = 0;
-  for (int slice = 0; slice < pl.slices; ++slice) {
+  int buf = s0;
+  for (int slice = s0; slice < s1; ++slice) {
     const char* ab = lds + buf * pl.vecs * 16;
     constexpr int CPR = F32 || sizeof(T) == 1 ? 2 : 1;  // A chunks per round
     int a0[FM];
@@ -343,7 +359,19 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_direct(ConvArgs a, DirectPl
     for (int j = 0; j < FN; ++j) bp[j] += U * LOADS * 1024;
     const int cur = buf;
     buf = buf + 1 == pl.nbuf ? 0 : buf + 1;
-    if (pl.nbuf < pl.slices && slice + 1 < pl.slices) {
+    if constexpr (FOLD)
+      if ((slice + 1) % pl.per == 0 || slice + 1 == pl.slices)
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              tot[i][j][e] += acc[i][j][e] + acc2[i][j][e];
+              acc[i][j][e] = 0.f;
+              acc2[i][j][e] = 0.f;
+            }
+    if (KS == 1 && pl.nbuf < pl.slices && slice + 1 < pl.slices) {
       // The next slice was issued at least a whole slice of weight loads
       // ago, so it has landed for this wave once those weights were used
       // (loads return in order; at most the D rounds ahead are still in
@@ -361,7 +389,37 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_direct(ConvArgs a, DirectPl
 #pragma unroll
       for (int j = 0; j < FN; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] += acc2[i][j][e];
+        for (int e = 0; e < 16; ++e) {
+          if constexpr (FOLD)
+            acc[i][j][e] = tot[i][j][e];
+          else
+            acc[i][j][e] += acc2[i][j][e];
+        }
+  }
+  if constexpr (KS > 1) {
+    // The parts go where the halo was (a part's slice is at least twice its
+    // 4 KiB); the first wave adds them and stores the tile.
+    float4* part = reinterpret_cast<float4*>(dsm);
+    __syncthreads();
+    if (s0 < s1)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        part[(kw * 4 + g) * 64 + lane] =
+            make_float4(acc[0][0][4 * g], acc[0][0][4 * g + 1], acc[0][0][4 * g + 2], acc[0][0][4 * g + 3]);
+    __syncthreads();
+    if (kw != 0) return;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[0][0][e] = 0.f;
+    const int n_parts = (pl.slices + pl.per - 1) / pl.per;
+    for (int k = 0; k < n_parts; ++k)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 v = part[(k * 4 + g) * 64 + lane];
+        acc[0][0][4 * g] += v.x;
+        acc[0][0][4 * g + 1] += v.y;
+        acc[0][0][4 * g + 2] += v.z;
+        acc[0][0][4 * g + 3] += v.w;
+      }
   }
 
   // Lane l holds, for fragment (i, j), pixel i*32 + l%32 of the wave tile
@@ -516,13 +574,13 @@ inline bool direct_ok(const ConvArgs& a) {
          (a.transposed != 2 || a.n_rows == 4 * a.cout) && (long)a.Hi * a.Wi * a.in_ld < (1L << 31);
 }
 
-template <typename T, int TAPS, int ST, int FM, int FN, int WM, int WN, int D, int PA>
+template <typename T, int TAPS, int ST, int FM, int FN, int WM, int WN, int D, int PA, int KS = 1, bool FOLD = false>
 hipError_t launch_direct(const ConvArgs& a, hipStream_t s) {
-  constexpr int NT = 64 * WM * WN, BM = 32 * FM * WM, BN = 32 * FN * WN;
+  constexpr int NT = 64 * WM * WN * KS, BM = 32 * FM * WM, BN = 32 * FN * WN;
   if (!direct_ok<T>(a) || a.taps != TAPS || a.stride != ST || a.tile_w <= 0 || BM % a.tile_w != 0 ||
       (a.transposed == 2 && a.cout > BN))
     return hipErrorInvalidValue;
-  const DirectPlan pl = direct_plan<T, NT, BN>(a, BM);
+  const DirectPlan pl = direct_plan<T, NT, BN>(a, BM, KS > 1);
   if (pl.nbuf == 0 || pl.loads > direct_loads(BM, ST, NT)) return hipErrorInvalidValue;
   const int th = BM / a.tile_w;
   const long blocks = (long)a.n_img * ((a.Ho + th - 1) / th) * ((a.Wo + a.tile_w - 1) / a.tile_w) *
@@ -530,7 +588,7 @@ hipError_t launch_direct(const ConvArgs& a, hipStream_t s) {
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
   if (blocks == 0) return hipSuccess;
   const size_t lds = (size_t)pl.nbuf * pl.vecs * 16 + 3 * BN * 4;
-  hipLaunchKernelGGL((conv_direct<T, TAPS, ST, FM, FN, WM, WN, D, PA>), dim3((unsigned)blocks), dim3(NT), lds, s, a,
+  hipLaunchKernelGGL((conv_direct<T, TAPS, ST, FM, FN, WM, WN, D, PA, KS, FOLD>), dim3((unsigned)blocks), dim3(NT), lds, s, a,
                      pl);
   return hipGetLastError();
 }
