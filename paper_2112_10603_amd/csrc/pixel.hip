@@ -73,10 +73,10 @@ __device__ inline void pack_chunks(const float (&v)[N], uint4 (&c)[N * sizeof(T)
 // of the wave's span, so every line is written in NC partial pieces and the
 // write requests multiply by NC (measured: the 48-byte records of the stage
 // transition took 5.5 of its 8.6 ms at 1080p x 112 views). Instead each lane
-// puts its record into the wave's LDS area (stage_put), the block meets at a
-// barrier, and each store instruction then writes 64 consecutive chunks
-// (stage_flush); records of pixels at or past the last valid one are not
-// written. These stores, and the final pass's blended image, are marked
+// puts its record into the wave's LDS area (stage_put) and, a wave's LDS
+// accesses being in order (wave_sync holds the compiler to it), each store
+// instruction then writes 64 consecutive chunks (stage_flush); records of
+// pixels at or past the row's last one are not written. These stores, and the final pass's blended image, are marked
 // non-temporal: a pass streams out far more than the caches hold, so
 // keeping its output lines cached only evicts the camera rows and flow
 // taps its waves are still gathering (measured at 1080p x 112 views: final
@@ -92,6 +92,12 @@ __device__ inline void store_nt(uint4* dst, const uint4& w) {
 __device__ inline void store_nt(float* dst, const float4& w) {
   const f32x4 v = {w.x, w.y, w.z, w.w};
   __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(dst));
+}
+
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 template <int NC>
@@ -125,22 +131,33 @@ __device__ inline void load8(const T* src, float (&v)[8]) {
   }
 }
 
-// Workgroup order of a (pixel blocks x views) grid for the final warp and
-// blend. Consecutive workgroup ids go to the 8 XCDs in turn, each with its
-// own L2; every XCD instead takes a contiguous range of an order that
-// visits one pixel block of every view before the next block, so the views
-// of a camera pair running together on an XCD read the same camera rows
-// from its L2. (Measured: 11 % faster for the final pass at 1080p x 112
-// views; the stage transition, whose output streams are wider, and the
-// other passes measured equal or slower with it.)
-__device__ inline void view_fastest_order(long& bx, int& v) {
-  const unsigned long gx = gridDim.x, gy = gridDim.y;
-  const unsigned long total = gx * gy;
-  const unsigned long id = (unsigned long)blockIdx.y * gx + blockIdx.x;
-  const unsigned long q = total >> 3, r = total & 7, x = id & 7;
-  const unsigned long lg = x * q + (x < r ? x : r) + (id >> 3);
-  bx = (long)(lg / gy);
-  v = (int)(lg - (unsigned long)bx * gy);
+// Workgroups of the passes that warp full images take 64 x 4 pixel tiles (a
+// wave a row of 64): the bilinear taps of a tile's rows overlap, and where
+// the flow is rough they scatter over neighbouring rows, which a tile keeps
+// in its L1 and a run of one row does not. Consecutive workgroup ids go to
+// the 8 XCDs in turn, each with its own L2, so an XCD takes columns of
+// kSuper tiles one above the other, the XCDs side by side in the same image
+// rows. views_fast: a column's tile in every view before the next tile, so
+// that views of one camera pair share its rows in the L2; otherwise view
+// after view, which keeps fewer output streams open at a time. Smooth flow /
+// flow with 4 pixels of noise, us, rows of 256 pixels -> tiles: final pass of
+// 4 views of 4K 827 -> 764 / 1427 -> 1022 (128 bytes a pixel: 5.6 / 4.2
+// TB/s), 24 of 1080p 1147 -> 1074 / 1635 -> 1382, one of 720p 18.5 -> 19.8 /
+// 23.5 -> 21.5; stage transition of 4 views of 4K 940 -> 869 / 1114 -> 959, 3
+// of 1080p 137 -> 91 / 161 -> 100, one of 720p 28 -> 19.5 / 33 -> 20.
+constexpr int kSuper = 8;
+inline dim3 super_grid(int h, int w, int n_views, bool views_fast) {
+  const long cols = (w + 63) / 64, sup = cols * (((h + 3) / 4 + kSuper - 1) / kSuper);
+  const unsigned sup8 = (unsigned)((sup + 7) / 8), n = (unsigned)n_views;
+  return views_fast ? dim3(8 * n, kSuper, sup8) : dim3(8 * kSuper, sup8, n);
+}
+// The tile (x, y) and view of this workgroup in a launch of images w wide.
+__device__ inline void super_tile(int w, bool views_fast, int& tx, int& ty, int& v) {
+  const int q = blockIdx.x >> 3, cols = (w + 63) / 64;
+  v = views_fast ? q : (int)blockIdx.z;
+  const unsigned sup = (views_fast ? blockIdx.z : blockIdx.y) * 8 + (blockIdx.x & 7), sy = sup / (unsigned)cols;
+  tx = (int)(sup - sy * cols);
+  ty = (int)(sy * kSuper) + (views_fast ? (int)blockIdx.y : q);
 }
 
 // Workgroup order within one image of a (pixel blocks x images) grid, for
@@ -153,9 +170,8 @@ __device__ inline void view_fastest_order(long& bx, int& v) {
 // same image at the same time (its cameras' rows stay shared in the
 // last-level cache). Measured at 1080p x 112 views: L2 misses of the
 // context warps fall 3.3x and of the head 2.1x, for 5-15 % and 2 % less
-// time (these passes wait on latency more than on bytes); the stage
-// transition, whose record writes dominate, runs 10 % slower with it and
-// keeps the launch order.
+// time (these passes wait on latency more than on bytes). (The context warps
+// in tiles four rows high measured 2 to 10 % slower than in this order.)
 __device__ inline long banded(unsigned i, unsigned gx) {  // block i of gx
   // the blocks of this image with the same id mod 8 share an XCD
   const unsigned r = i & 7u, q = gx >> 3, rem = gx & 7u;
@@ -295,22 +311,20 @@ __global__ void assemble0_k(const ViewDesc* views, const CamDev* cams, int h, in
 template <typename T>
 __global__ __launch_bounds__(TPB) void transition_k(const ViewDesc* views, const CamDev* cams, int level,
                                                     const float* FMprev, int hp, int wp, int h, int w, T* x,
-                                                    int ld, float* FM, int t_plane) {
+                                                    int ld, float* FM, int t_plane, bool views_fast) {
   constexpr int NX = 24 * (int)sizeof(T) / 16;  // chunks of a pixel's 24 activations
   __shared__ uint4 stage[TPB * (NX + 2)];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int v = blockIdx.y;
-  const long bx = blockIdx.x;  // launch order: measured faster here than banded_block()
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int tx, ty, v;
+  super_tile(w, views_fast, tx, ty, v);
   const long P = (long)h * w;  // slot strides: P here, hp * wp for the previous level
   const ViewDesc d = views[v];
   const int vh = d.hp >> (2 - level), vw = d.wp >> (2 - level);  // this view's level sizes
   const int vhp = vh >> 1, vwp = vw >> 1;
-  const long n_px = (long)vh * vw;
-  const long p0 = bx * TPB + wave * 64;  // the wave's first pixel
-  if (bx * TPB >= n_px) return;  // uniform over the block
-  // lanes past the view's last pixel compute pixel 0 and store nothing
-  const long p = p0 + lane < n_px ? p0 + lane : 0;
-  const int y = (int)(p / vw), xx = (int)(p % vw);
+  const int y = ty * 4 + wave, xb = tx * 64;  // the wave's first pixel
+  if (y >= vh || xb >= vw) return;  // uniform over the wave; waves share nothing
+  const int xx = min(xb + lane, vw - 1);  // lanes past the row's end repeat its last pixel and store nothing
+  const int p = y * vw + xx;
   int y0, y1, x0, x1;
   float by, ax;
   hp_tap(y, vhp, vh, y0, y1, by);
@@ -328,7 +342,7 @@ __global__ __launch_bounds__(TPB) void transition_k(const ViewDesc* views, const
 
   const float* Lc = level == 1 ? cams[d.cam_l].L1 : cams[d.cam_l].X4;
   const float* Rc = level == 1 ? cams[d.cam_r].L1 : cams[d.cam_r].X4;
-  const float4 L = ld4(Lc + 4 * p), R = ld4(Rc + 4 * p);
+  const float4 L = ld4(Lc + 4L * p), R = ld4(Rc + 4L * p);
   const float4 Wl = sample4(Lc, warp_taps(xx, y, Fx, Fy, vw, vh));
   const float4 Wr = sample4(Rc, warp_taps(xx, y, Gx, Gy, vw, vh));
 
@@ -342,10 +356,11 @@ __global__ __launch_bounds__(TPB) void transition_k(const ViewDesc* views, const
   uint4* sf = stage + TPB * NX + wave * 128;
   stage_put<NX>(sx, lane, cx);
   stage_put<2>(sf, lane, cf);
-  __syncthreads();
-  const int n_valid = (int)(n_px - p0 < 64 ? n_px - p0 : 64);
-  stage_flush<NX>(sx, lane, reinterpret_cast<uint4*>(x + ((long)v * P + p0) * ld), n_valid);
-  stage_flush<2>(sf, lane, reinterpret_cast<uint4*>(FM + ((long)v * P + p0) * 8), n_valid);
+  wave_sync();
+  const int n_valid = min(64, vw - xb);
+  const long p0 = (long)v * P + (long)y * vw + xb;
+  stage_flush<NX>(sx, lane, reinterpret_cast<uint4*>(x + p0 * ld), n_valid);
+  stage_flush<2>(sf, lane, reinterpret_cast<uint4*>(FM + p0 * 8), n_valid);
 }
 
 // ------------------------------------ final warp + mask blend (Eq. 1)
@@ -354,26 +369,24 @@ __global__ __launch_bounds__(TPB) void final_k(const ViewDesc* views, const CamD
                                                int h, int w, float* I2, T* x0u, int ld) {
   constexpr int NX = 24 * (int)sizeof(T) / 16;  // chunks of a pixel's 24 activations
   __shared__ uint4 stage[TPB * NX];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  long bx;
-  int v;
-  view_fastest_order(bx, v);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int tx, ty, v;
+  super_tile(w, true, tx, ty, v);
   const long P = (long)h * w;  // slot stride
   const ViewDesc d = views[v];
   const int vh = d.hp, vw = d.wp;  // this view's size
-  const long n_px = (long)vh * vw;
-  const long p0 = bx * TPB + wave * 64;  // the wave's first pixel
-  if (bx * TPB >= n_px) return;  // uniform over the block
-  // lanes past the view's last pixel compute pixel 0 and store nothing
-  const bool in = p0 + lane < n_px;
-  const long p = in ? p0 + lane : 0;
-  const int y = (int)(p / vw), xx = (int)(p % vw);
+  const int y = ty * 4 + wave, xb = tx * 64;  // the wave's first pixel
+  if (y >= vh || xb >= vw) return;  // uniform over the wave; waves share nothing
+  // lanes past the row's end repeat its last pixel and store nothing
+  const bool in = xb + lane < vw;
+  const int xx = in ? xb + lane : vw - 1;
+  const int p = y * vw + xx;
   const float* f = FM + ((long)v * P + p) * 8;
   const float4 F = ld4(f);
   const float M = f[4];
   const float* Lc = cams[d.cam_l].X4;
   const float* Rc = cams[d.cam_r].X4;
-  const float4 L = ld4(Lc + 4 * p), R = ld4(Rc + 4 * p);
+  const float4 L = ld4(Lc + 4L * p), R = ld4(Rc + 4L * p);
   const float4 Wl = sample4(Lc, warp_taps(xx, y, F.x, F.y, vw, vh));
   const float4 Wr = sample4(Rc, warp_taps(xx, y, F.z, F.w, vw, vh));
   const float m = 1.f / (1.f + expf(-M));
@@ -389,9 +402,8 @@ __global__ __launch_bounds__(TPB) void final_k(const ViewDesc* views, const CamD
   pack_chunks<T, 24>(vals, cx);
   uint4* sx = stage + wave * 64 * NX;
   stage_put<NX>(sx, lane, cx);
-  __syncthreads();
-  const int n_valid = (int)(n_px - p0 < 64 ? n_px - p0 : 64);
-  stage_flush<NX>(sx, lane, reinterpret_cast<uint4*>(x0u + ((long)v * P + p0) * ld), n_valid);
+  wave_sync();
+  stage_flush<NX>(sx, lane, reinterpret_cast<uint4*>(x0u + ((long)v * P + (long)y * vw + xb) * ld), min(64, vw - xb));
 }
 
 // ------------------------------- blend-only output (no refinement, Table 1)
@@ -757,12 +769,17 @@ hipError_t launch_transition(const ViewDesc* views, int n_views, const CamDev* c
                              float* FM, DType dt, int t_plane, hipStream_t s) {
   if (n_views <= 0) return hipSuccess;
   if (ld != 24) return hipErrorInvalidValue;  // 18 channels padded to 24 (16-byte runs)
+  // Views fastest up to 16 M pixels a launch; beyond, the records written are
+  // gigabytes and HBM prefers fewer streams. us, views fastest / view after
+  // view: 6 views of 1080p 176 / 223, 12 of 1080p (25 M pixels) 686 / 638, 4
+  // of 4K 929 / 869.
+  const bool fast = (long)n_views * h * w <= 16 << 20;
   if (dt == DType::F32)
-    hipLaunchKernelGGL(transition_k<float>, grid1((long)h * w, n_views), dim3(TPB), 0, s, views, cams,
-                       level, FMprev, hp, wp, h, w, (float*)x, ld, FM, t_plane);
+    hipLaunchKernelGGL(transition_k<float>, super_grid(h, w, n_views, fast), dim3(TPB), 0, s, views, cams,
+                       level, FMprev, hp, wp, h, w, (float*)x, ld, FM, t_plane, fast);
   else
-    hipLaunchKernelGGL(transition_k<bf16>, grid1((long)h * w, n_views), dim3(TPB), 0, s, views, cams,
-                       level, FMprev, hp, wp, h, w, (bf16*)x, ld, FM, t_plane);
+    hipLaunchKernelGGL(transition_k<bf16>, super_grid(h, w, n_views, fast), dim3(TPB), 0, s, views, cams,
+                       level, FMprev, hp, wp, h, w, (bf16*)x, ld, FM, t_plane, fast);
   return hipGetLastError();
 }
 
@@ -771,10 +788,10 @@ hipError_t launch_final(const ViewDesc* views, int n_views, const CamDev* cams, 
   if (n_views <= 0) return hipSuccess;
   if (ld != 24) return hipErrorInvalidValue;  // 17 channels padded to 24 (16-byte runs)
   if (dt == DType::F32)
-    hipLaunchKernelGGL(final_k<float>, grid1((long)h * w, n_views), dim3(TPB), 0, s, views, cams, FM, h,
+    hipLaunchKernelGGL(final_k<float>, super_grid(h, w, n_views, true), dim3(TPB), 0, s, views, cams, FM, h,
                        w, I2, (float*)x0u, ld);
   else
-    hipLaunchKernelGGL(final_k<bf16>, grid1((long)h * w, n_views), dim3(TPB), 0, s, views, cams, FM, h,
+    hipLaunchKernelGGL(final_k<bf16>, super_grid(h, w, n_views, true), dim3(TPB), 0, s, views, cams, FM, h,
                        w, I2, (bf16*)x0u, ld);
   return hipGetLastError();
 }
