@@ -623,24 +623,30 @@ __global__ void head_k(const T* u4, int ld, const float* wgt, const float* bias,
 
 // The same head for bf16 activations on the matrix cores: the 3x3 conv is a
 // GEMM with the 3 output channels (zero-padded to 32) as the A operand and
-// 32 pixels as B, K = (tap, channel) in 16-channel MFMA steps. A wave
-// computes groups of 32 consecutive pixels of the crop: lane l reads, per
-// tap, the 8 channels 8*(l/32).. of pixel l%32's neighbour (one 16-byte
-// load), and ends with that pixel's three pre-activations in its first
-// accumulators (lanes 0-31). The weights are rounded to bf16 (as every other
-// bf16 layer's) and laid out once per block as MFMA fragments in LDS; a
-// block covers up to HEAD_GROUPS groups per wave to amortise that, fewer
-// where the launch would leave compute units without a block.
-constexpr int HEAD_GROUPS = 32;
+// 32 pixels as B, K = (tap, channel) in 16-channel MFMA steps. A wave walks
+// down a strip of 32 pixels of a row, two rows a step: lane l holds the 8
+// channels 8*(l/32).. of pixel l%32's three horizontal neighbours in each of
+// the four rows that the two results need, of which two are loaded per step
+// (one 16-byte load a tap). Each result ends with its pixels' three
+// pre-activations in the first accumulators of lanes 0-31; the second row's
+// move to lanes 32-63, so that all lanes share the sigmoid, the blend and the
+// stores. The weights are rounded to bf16 (as every other bf16 layer's) and
+// laid out once per block as MFMA fragments in LDS.
+//
+// Bound by the latency of its loads at four waves per SIMD (128 registers; a
+// step of prefetch costs a wave and measured equal). Groups of 32 pixels that
+// loaded all nine taps, divided a 64-bit index and left half the lanes idle
+// in the sigmoid were bound by instructions: 4 views of 4K 832 -> 600 us (60
+// bytes a pixel: 3.3 TB/s), 24 of 1080p 1196 -> 882, one of 720p 25 -> 20;
+// 32 channels, 4 views of 4K 1472 -> 996.
 // threads per block of the MFMA head: eight waves share one weight table
 // (measured 6 % faster than four at 1080p x 112 views)
 constexpr int HEAD_TPB = 512;
 
 template <int C>
-__global__ __launch_bounds__(HEAD_TPB) void head_mfma_k(const bf16* u4, int ld, const float* wgt,
+__global__ __launch_bounds__(HEAD_TPB, C == 16 ? 4 : 2) void head_mfma_k(const bf16* u4, int ld, const float* wgt,
                                                    const float* bias, const float* I2,
-                                                   const ViewDesc* views, int Hp, int Wp, int H, int W,
-                                                   int groups) {
+                                                   const ViewDesc* views, int Hp, int Wp, int rows) {
   constexpr int NC = C / 16;  // MFMAs per tap
   constexpr int WAVES = HEAD_TPB / 64;
   __shared__ uint4 wtab[9 * NC * 64];  // [tap][j][lane] weight fragments
@@ -653,59 +659,95 @@ __global__ __launch_bounds__(HEAD_TPB) void head_mfma_k(const bf16* u4, int ld, 
     wtab[i] = __builtin_bit_cast(uint4, w);
   }
   __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lrow = lane & 31, lhalf = lane >> 5;
   const int v = blockIdx.y;
-  const long bx = banded_block();
   const ViewDesc d = views[v];
   const long slot = (long)v * Hp * Wp;  // slot stride of the launch's size
   // this view's size from here on
-  H = d.h;
-  W = d.w;
-  Hp = d.hp;
-  Wp = d.wp;
-  const long HW = (long)H * W;
+  const int H = d.h, W = d.w, hp = d.hp, wp = d.wp;
+  const int cols = (W + 31) / 32;
+  const int strip = (int)banded_block() * WAVES + wave, sy = strip / cols;
+  const int x0 = (strip - sy * cols) * 32, y0 = sy * rows, y1 = min(y0 + rows, H);
+  if (y0 >= H) return;  // uniform over the wave
   const bf16* base = u4 + slot * ld + 8 * lhalf;
   const float bias0 = bias[0], bias1 = bias[1], bias2 = bias[2];
-  float* o = d.out;
-  // One group per iteration: its nine tap loads and the blend input go out
-  // together and wait for one memory round trip. (Two groups per
-  // iteration halve the round trips but need 132 registers, three waves
-  // per SIMD; one group keeps more waves resident and measured 16 % faster
-  // at 1080p x 112 views.)
-  for (int g = 0; g < groups; ++g) {
-    if ((bx * groups + g) * WAVES * 32 >= HW) break;  // uniform over the block
-    const long p = ((bx * groups + g) * WAVES + wave) * 32 + lrow;
-    const bool pin = p < HW;
-    const int y = pin ? (int)(p / W) : 0;
-    const int x = pin ? (int)(p % W) : 0;
-    uint4 av[9][NC];
+  const long HW = (long)H * W;
+  const int x = x0 + lrow;
+  // the three columns, clamped into the row, and whether they lie in it
+  const bool inside = x0 > 0 && x0 + 32 < wp;  // uniform
+  int xo[3];
+  bool xk[3];
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
-      const bool ok = pin && yy >= 0 && yy < Hp && xx >= 0 && xx < Wp;  // zero padding
-      const bf16* src = base + ((long)(ok ? yy : 0) * Wp + (ok ? xx : 0)) * ld;
+  for (int t = 0; t < 3; ++t) {
+    xk[t] = x + t >= 1 && x + t <= wp;
+    xo[t] = min(max(x + t - 1, 0), wp - 1) * ld;
+  }
+  uint4 win[4][3][NC];  // rows y - 1 .. y + 2
+  auto load_row = [&](uint4 (&r)[3][NC], int yy) {
+    if (yy < 0 || yy >= hp) {  // uniform: zero padding
 #pragma unroll
-      for (int j = 0; j < NC; ++j)
-        av[tap][j] = ok ? *reinterpret_cast<const uint4*>(src + 16 * j) : make_uint4(0u, 0u, 0u, 0u);
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) r[t][j] = make_uint4(0u, 0u, 0u, 0u);
+      return;
     }
-    const float4 b = ld4(I2 + (slot + (long)y * Wp + x) * 4);
-    f32x16 acc;
+    const bf16* src = base + (long)yy * wp * ld;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int j = 0; j < NC; ++j) r[t][j] = *reinterpret_cast<const uint4*>(src + xo[t] + 16 * j);
+    if (!inside)
+#pragma unroll
+      for (int t = 0; t < 3; t += 2)
+        if (!xk[t])
+#pragma unroll
+          for (int j = 0; j < NC; ++j) r[t][j] = make_uint4(0u, 0u, 0u, 0u);
+  };
+  load_row(win[0], y0 - 1);
+  load_row(win[1], y0);
+  for (int y = y0; y < y1; y += 2) {
+    const int yl = y + lhalf;
+    const bool in = x < W && yl < H;
+    load_row(win[2], y + 1);
+    load_row(win[3], y + 2);
+    const float4 b = ld4(I2 + (slot + (in ? (long)yl * wp + x : 0)) * 4);
+    f32x16 acc[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[r][e] = 0.f;
 #pragma unroll
     for (int tap = 0; tap < 9; ++tap)
 #pragma unroll
-      for (int j = 0; j < NC; ++j)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wtab[(tap * NC + j) * 64 + lane]),
-                                                      __builtin_bit_cast(bf16x8, av[tap][j]), acc, 0, 0, 0);
-    if (lhalf == 0 && pin) {
-      const float z0 = acc[0] + bias0, z1 = acc[1] + bias1, z2 = acc[2] + bias2;
-      const float r0 = 1.f / (1.f + expf(-z0)), r1 = 1.f / (1.f + expf(-z1)), r2 = 1.f / (1.f + expf(-z2));
-      o[p] = fminf(fmaxf(b.x + 2.f * r0 - 1.f, 0.f), 1.f);
-      o[HW + p] = fminf(fmaxf(b.y + 2.f * r1 - 1.f, 0.f), 1.f);
-      o[2 * HW + p] = fminf(fmaxf(b.z + 2.f * r2 - 1.f, 0.f), 1.f);
+      for (int j = 0; j < NC; ++j) {
+        const bf16x8 w = __builtin_bit_cast(bf16x8, wtab[(tap * NC + j) * 64 + lane]);
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+          acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              w, __builtin_bit_cast(bf16x8, win[r + tap / 3][tap % 3][j]), acc[r], 0, 0, 0);
+      }
+    float z[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      z[c] = __uint_as_float(
+          __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[0][c]), __float_as_uint(acc[1][c]), false, false)[0]);
+    z[0] += bias0;
+    z[1] += bias1;
+    z[2] += bias2;
+    if (in) {
+      const float r0 = 1.f / (1.f + expf(-z[0])), r1 = 1.f / (1.f + expf(-z[1])), r2 = 1.f / (1.f + expf(-z[2]));
+      float* o = d.out + (long)yl * W + x;
+      o[0] = fminf(fmaxf(b.x + 2.f * r0 - 1.f, 0.f), 1.f);
+      o[HW] = fminf(fmaxf(b.y + 2.f * r1 - 1.f, 0.f), 1.f);
+      o[2 * HW] = fminf(fmaxf(b.z + 2.f * r2 - 1.f, 0.f), 1.f);
     }
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) win[r][t][j] = win[r + 2][t][j];
   }
 }
 
@@ -839,21 +881,19 @@ hipError_t launch_head(const void* u4, int ld, int C, const float* w, const floa
   if (n_img <= 0) return hipSuccess;
   if (C <= 0 || C > 64 || C % 8 != 0 || C > ld || ld % 8 != 0) return hipErrorInvalidValue;
   if (dt == DType::BF16 && (C == 16 || C == 32)) {
-    // At least two blocks per compute unit (as many as fit at a time) before
-    // a block's weight table is spread over more groups: one 720p view 63 us
-    // with 32 groups (113 blocks), 29 with 4 (900 blocks) and with 2; one
-    // 270x481 view 59 -> 7 us.
-    int groups = HEAD_GROUPS;
-    const long units = ((long)H * W + (HEAD_TPB / 64) * 32 - 1) / ((HEAD_TPB / 64) * 32) * n_img;
-    while (groups > 1 && units / groups < 512) groups >>= 1;
-    const long per_block = (long)groups * (HEAD_TPB / 64) * 32;
-    const dim3 g((unsigned)(((long)H * W + per_block - 1) / per_block), (unsigned)n_img);
+    // Strips of up to 32 rows (a strip reads two more than it writes), fewer
+    // where the launch would leave compute units with less than a few
+    // blocks. us by rows of a strip: one view of 720p 64: 64, 32: 36, 16: 22,
+    // 8 (450 blocks): 20, 4: 21; one of 1080p 32: 38, 16 (510): 33, 8: 39; 5
+    // of 1136x848 32 (608): 109, 16: 93, 8: 96; 4 of 4K 32: 598, 16: 622.
+    int rows = 32;
+    auto blocks = [&] { return (((W + 31) / 32) * (long)((H + rows - 1) / rows) + HEAD_TPB / 64 - 1) / (HEAD_TPB / 64); };
+    while (rows > 2 && blocks() * n_img < (rows > 16 ? 1024 : 384)) rows >>= 1;
+    const dim3 g((unsigned)blocks(), (unsigned)n_img);
     if (C == 16)
-      hipLaunchKernelGGL(head_mfma_k<16>, g, dim3(HEAD_TPB), 0, s, (const bf16*)u4, ld, w, b, I2, views, Hp, Wp,
-                         H, W, groups);
+      hipLaunchKernelGGL(head_mfma_k<16>, g, dim3(HEAD_TPB), 0, s, (const bf16*)u4, ld, w, b, I2, views, Hp, Wp, rows);
     else
-      hipLaunchKernelGGL(head_mfma_k<32>, g, dim3(HEAD_TPB), 0, s, (const bf16*)u4, ld, w, b, I2, views, Hp, Wp,
-                         H, W, groups);
+      hipLaunchKernelGGL(head_mfma_k<32>, g, dim3(HEAD_TPB), 0, s, (const bf16*)u4, ld, w, b, I2, views, Hp, Wp, rows);
     return hipGetLastError();
   }
   const dim3 grid = grid1((long)H * W, n_img);
