@@ -33,7 +33,9 @@
 // the result does not depend on scheduling.
 //
 // Measured (one MI355X, whole call): 8 x 3 x 256 x 448 with gradient 561 ->
-// 89 us, 1 x 3 x 1079 x 1917 without 2637 -> 81 us. Before, one thread
+// 84 us, 1 x 3 x 1079 x 1917 without 2632 -> 73 us. (The bands formed in the
+// tiles of the reduce passes, which saves their second read, took 90 and 75:
+// the tiles' LDS work outweighs a read that hits the caches.) Before, one thread
 // summed all partials of an image, each level had its own launches, seeds
 // were floats, and the border gathers walked 9 x 9 taps.
 #include <algorithm>
@@ -179,7 +181,8 @@ struct BandArgs {
   const float* gt;
   const float* G[kLapLevels + 1];  // levels 1..5
   uint8_t* S[kLapLevels];          // packed signs per quad, or null
-  double* partial;                 // [plane][first[5]]
+  double* partial;                 // [plane][first[5]], weighted
+  double weight[kLapLevels];
   int first[kLapLevels + 1];
 };
 template <typename A>
@@ -255,38 +258,31 @@ __global__ __launch_bounds__(TPB) void band_k(BandArgs t) {
     double s = 0.0;
 #pragma unroll
     for (int i = 0; i < TPB / 64; ++i) s += (double)wsum[i];
-    t.partial[plane * gridDim.x + blockIdx.x] = s;
+    t.partial[plane * gridDim.x + blockIdx.x] = t.weight[l] * s;
   }
 }
 
-// loss[img] = sum over levels of weight * (sum of the level's partials of
-// the image's 3 planes): one workgroup per image, each thread a fixed
-// strided share, then a fixed tree, in double. (One thread per image took
-// 2.4 of the 2.6 ms of a 1079 x 1917 loss.)
-struct SumArgs {
-  const double* partial;
-  int first[kLapLevels + 1];
-  double weight[kLapLevels];
-  float* loss;
-};
-__global__ __launch_bounds__(TPB) void sum_k(SumArgs t) {
-  const int n = t.first[kLapLevels];
-  const double* p = t.partial + (long)blockIdx.x * 3 * n;
+// loss[img] = sum of the image's n partials: one workgroup per image, each
+// thread a fixed strided share with its loads in flight together, then a
+// fixed tree, in double. (One thread per image took 2.4 of the 2.6 ms of a
+// 1079 x 1917 loss; 256 threads that walked plane by plane and level by level
+// 11 us, these 4.)
+constexpr int kSumTPB = 1024;
+__global__ __launch_bounds__(kSumTPB) void sum_k(const double* partial, int n, float* loss) {
+  const double* p = partial + (long)blockIdx.x * n;
   double total = 0.0;
-  for (int l = 0; l < kLapLevels; ++l) {
-    double s = 0.0;
-    for (int pl = 0; pl < 3; ++pl)
-      for (int i = t.first[l] + threadIdx.x; i < t.first[l + 1]; i += TPB) s += p[(long)pl * n + i];
-    total += t.weight[l] * s;
-  }
-  __shared__ double red[TPB];
-  red[threadIdx.x] = total;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += kSumTPB) total += p[i];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
+  __shared__ double red[kSumTPB / 64];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = total;
   __syncthreads();
-  for (int k = TPB / 2; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0.0;
+    for (int i = 0; i < kSumTPB / 64; ++i) s += red[i];
+    loss[blockIdx.x] = (float)s;
   }
-  if (threadIdx.x == 0) t.loss[blockIdx.x] = (float)red[0];
 }
 
 // E_(i+1) = E^T(s_i) on level i + 1, all levels: E^T(s)[p][q] =
@@ -529,24 +525,21 @@ hipError_t launch_lap_loss(const float* x, const float* gt, int n_img, int H, in
   for (int i = 0; i < kLapLevels; ++i)
     weight[i] = (double)(1 << i) / (3.0 * (double)L.h[i] * L.w[i]);  // 2^(i-1) / N_i, N_i = 3 h w
   BandArgs b{};
-  SumArgs m{};
   b.L = L;
   b.x = x;
   b.gt = gt;
   b.partial = P.partial;
-  m.partial = P.partial;
-  m.loss = loss;
   for (int i = 0; i <= kLapLevels; ++i) {
     b.G[i] = P.G[i];
-    b.first[i] = m.first[i] = P.first[i];
+    b.first[i] = P.first[i];
     if (i < kLapLevels) {
       b.S[i] = P.S[i];
-      m.weight[i] = weight[i];
+      b.weight[i] = weight[i];
     }
   }
   hipLaunchKernelGGL(band_k, all, dim3(TPB), 0, s, b);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(sum_k, dim3((unsigned)n_img), dim3(TPB), 0, s, m);
+  hipLaunchKernelGGL(sum_k, dim3((unsigned)n_img), dim3(kSumTPB), 0, s, P.partial, 3 * P.first[kLapLevels], loss);
   if ((e = hipGetLastError()) != hipSuccess || !grad) return e;
 
   // backward: E^T of every level's signs, then T coarsest level first
