@@ -26,7 +26,8 @@
 // channels, 3x3). A tile that meets a value the split cannot hold (infinity,
 // NaN, or a magnitude that rounds past the largest bf16) gives a non-finite
 // accumulator; such a wave recomputes its outputs with plain fp32
-// multiply-adds.
+// multiply-adds. Layers with weights that the split cannot hold (split3.h)
+// have no weights in fragment order and run on the fp32 matrix instruction.
 //
 // What bounds it. Small grids: the chain of a workgroup's K rounds (144 for
 // 256 channels): dependent MFMAs are 64 cycles apart, 3.8 us in all, and about

@@ -19,6 +19,7 @@
 #include "fault.h"
 #include "serve.h"
 #include "sha256.h"
+#include "split3.h"
 
 namespace ffv {
 
@@ -26,15 +27,6 @@ namespace {
 
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
-// float -> bf16 bits, round to nearest even (NaN kept quiet).
-inline uint16_t f2bf(float f) {
-  uint32_t u;
-  std::memcpy(&u, &f, 4);
-  if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x7fffffu)) return (uint16_t)((u >> 16) | 0x40);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
 
 struct Expect {
   const char* kind;
@@ -309,7 +301,9 @@ static std::vector<uint8_t> fragment_order(const Layer& L, DType dt, int k_pad, 
 }
 
 bool direct_layer(const Layer& L, DType dt) {
-  return L.name != "unet.head" && (dt == DType::F32 || L.cin_pad % conv_k_step(dt) == 0);
+  if (L.name == "unet.head") return false;
+  if (dt == DType::F32) return std::all_of(L.w_host.begin(), L.w_host.end(), splittable);
+  return L.cin_pad % conv_k_step(dt) == 0;
 }
 
 std::vector<uint8_t> pack_direct(const Layer& L, DType dt) {
@@ -321,24 +315,15 @@ std::vector<uint8_t> pack_direct(const Layer& L, DType dt) {
   const size_t rows = (size_t)(L.mode == 1 ? 4 : 1) * L.cout_pad;
   std::vector<uint8_t> f(rows * k_pad * 6 + kDirectPad, 0);
   uint16_t* q = reinterpret_cast<uint16_t*>(f.data());
-  auto widen = [](uint16_t b) {
-    const uint32_t u = (uint32_t)b << 16;
-    float v;
-    std::memcpy(&v, &u, 4);
-    return v;
-  };
   for (size_t r0 = 0; r0 < rows; r0 += 32)
     for (int st = 0; st < slices * taps; ++st)
       for (int g = 0; g < 2; ++g, q += 3 * 512)
         for (int lane = 0; lane < 64; ++lane) {
           const float* src = &p[(r0 + lane % 32) * k_pad + (size_t)st * bk + (lane / 32) * 16 + g * 8];
           for (int e = 0; e < 8; ++e) {
-            const uint16_t h = f2bf(src[e]);
-            const float r = src[e] - widen(h);
-            const uint16_t m = f2bf(r);
-            q[lane * 8 + e] = h;
-            q[512 + lane * 8 + e] = m;
-            q[1024 + lane * 8 + e] = f2bf(r - widen(m));
+            uint16_t part[3];
+            split3(src[e], part);
+            for (int k = 0; k < 3; ++k) q[512 * k + lane * 8 + e] = part[k];
           }
         }
   return f;

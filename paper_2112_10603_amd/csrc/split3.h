@@ -1,0 +1,43 @@
+// The exact split of a float into three bf16 parts, x = h + m + l (8 + 8 + 8
+// significand bits, each the rest rounded to nearest even), with which fp32
+// convolutions run on the bf16 matrix cores. Host side: the packed weights.
+#pragma once
+
+#include <cmath>
+#include <cstdint>
+#include <cstring>
+
+namespace ffv {
+
+// float -> bf16 bits, round to nearest even (NaN kept quiet).
+inline uint16_t f2bf(float f) {
+  uint32_t u;
+  std::memcpy(&u, &f, 4);
+  if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x7fffffu)) return (uint16_t)((u >> 16) | 0x40);
+  u += 0x7fffu + ((u >> 16) & 1u);
+  return (uint16_t)(u >> 16);
+}
+
+inline float bf2f(uint16_t b) {
+  const uint32_t u = (uint32_t)b << 16;
+  float v;
+  std::memcpy(&v, &u, 4);
+  return v;
+}
+
+// part[0 .. 2] = h, m, l of w.
+inline void split3(float w, uint16_t part[3]) {
+  part[0] = f2bf(w);
+  const float r = w - bf2f(part[0]);
+  part[1] = f2bf(r);
+  part[2] = f2bf(r - bf2f(part[1]));
+}
+
+// Largest magnitude of a weight that is split. (h of one within half a bf16
+// unit of the largest float would round to infinity and m, l to minus
+// infinity and NaN; layers with larger, infinite or NaN weights run on the
+// fp32 matrix instruction.)
+constexpr float kSplitMax = 0x1p100f;
+inline bool splittable(float w) { return std::fabs(w) <= kSplitMax; }
+
+}  // namespace ffv
