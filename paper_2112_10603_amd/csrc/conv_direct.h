@@ -15,16 +15,16 @@
 // as in conv_kernel.h (whose slice-major layers it shares), with one fp32
 // accumulator per element for bf16 and fp8: the same results bit for bit.
 //
-// fp32 layers run on the bf16 matrix cores: every fp32 operand is split
-// exactly into three bf16 parts, x = h + m + l (8 + 8 + 8 significand bits,
-// each the rest rounded to nearest), activations in registers, weights when
-// they are packed, and the six products of weight 2^-16 and more are summed:
+// fp32 layers run on the bf16 matrix cores: every fp32 operand is scaled (see
+// split3.h) and split exactly into three bf16 parts, x = h + m + l (8 + 8 + 8
+// significand bits, each the rest rounded to nearest), activations in
+// registers, weights when they are packed, and the six products of weight 2^-16 and more are summed:
 // h*h in one fp32 accumulator, h*m, m*h, m*m, h*l, l*h in another, added at
 // the end. The dropped products are below 2^-26 of h*h. Rounding once per 16
 // products instead of once per 2, the error against float64 is smaller than
 // that of v_mfma_f32_32x32x2f32: 2.2e-7 against 6.0e-7 relative (256
 // channels, 3x3). A tile that meets a value the split cannot hold (infinity,
-// NaN, or a magnitude that rounds past the largest bf16) gives a non-finite
+// NaN, or a magnitude past 2^104) or a sum past 2^80 gives a non-finite
 // accumulator; such a wave recomputes its outputs with plain fp32
 // multiply-adds. Layers with weights that the split cannot hold (split3.h)
 // have no weights in fragment order and run on the fp32 matrix instruction.
@@ -44,6 +44,7 @@
 #pragma once
 
 #include "conv_kernel.h"
+#include "split3.h"
 
 namespace ffv {
 namespace convk {
@@ -300,14 +301,17 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void conv_direct(ConvArgs a, Dir
     // (at most five VALU instructions, 20 cycles) in the shadow of each.
     uint32_t sp[2][F32 ? FM : 1][3][4];
     float x0 = 0.f, x1 = 0.f;
+    auto fetch = [&](int u, int k) {  // the pair of third k
+      const int i = k / 12, q = k / 3 % 4;
+      const uint4& v = fa[u % (PA + 1)][i][(q >> 1) % CPR];
+      x0 = __uint_as_float(q & 1 ? v.z : v.x) * kSplitScale;
+      x1 = __uint_as_float(q & 1 ? v.w : v.y) * kSplitScale;
+    };
     auto split = [&](int u, int k) {  // third k of round u's split
       const int i = k / 12, q = k / 3 % 4, st = k % 3;
-      if (st == 0) {
-        const uint4& v = fa[u % (PA + 1)][i][(q >> 1) % CPR];
-        x0 = __uint_as_float(q & 1 ? v.z : v.x);
-        x1 = __uint_as_float(q & 1 ? v.w : v.y);
-      }
+      if (k == 0) fetch(u, 0);
       sp[u & 1][i][st][q] = split_stage(x0, x1, st);
+      if (st == 2 && k + 1 < 12 * FM) fetch(u, k + 1);
     };
     if constexpr (F32)
 #pragma unroll
@@ -442,6 +446,13 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void conv_direct(ConvArgs a, Dir
   };
 
   if constexpr (F32) {
+    constexpr float unscale = 1.f / (kSplitScale * kSplitScale);
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] *= unscale;
     bool bad = false;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -469,7 +480,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void conv_direct(ConvArgs a, Dir
                                  (ch & 1) * 4 + (c & 3);
             const float w = __uint_as_float((uint32_t)wp[0] << 16) + __uint_as_float((uint32_t)wp[512] << 16) +
                             __uint_as_float((uint32_t)wp[1024] << 16);
-            sum = fmaf(x[c], w, sum);
+            sum = fmaf(x[c], w * (1.f / kSplitScale), sum);
           }
         }
         const long pix = img_off + ((long)((oy << sh) + py) * a.Wout + (ox << sh) + px) * a.out_ld;

@@ -308,7 +308,7 @@ bool direct_layer(const Layer& L, DType dt) {
 
 std::vector<uint8_t> pack_direct(const Layer& L, DType dt) {
   if (dt != DType::F32) return fragment_order(L, dt, L.K_pad, pack_layer(L, dt));
-  // fp32: three bf16 parts per weight, w = h + m + l exactly
+  // fp32: three bf16 parts per scaled weight, exactly
   const int bk = conv_k_step(dt), taps = L.mode == 1 ? 4 : 9, slices = (L.cin_pad + bk - 1) / bk;
   const int k_pad = slices * taps * bk;
   const std::vector<float> p = pack_layer_f(L, bk, k_pad, L.w_host, true);
@@ -322,7 +322,7 @@ std::vector<uint8_t> pack_direct(const Layer& L, DType dt) {
           const float* src = &p[(r0 + lane % 32) * k_pad + (size_t)st * bk + (lane / 32) * 16 + g * 8];
           for (int e = 0; e < 8; ++e) {
             uint16_t part[3];
-            split3(src[e], part);
+            split3(src[e] * kSplitScale, part);
             for (int k = 0; k < 3; ++k) q[512 * k + lane * 8 + e] = part[k];
           }
         }

@@ -1,6 +1,11 @@
 // The exact split of a float into three bf16 parts, x = h + m + l (8 + 8 + 8
 // significand bits, each the rest rounded to nearest even), with which fp32
 // convolutions run on the bf16 matrix cores. Host side: the packed weights.
+// Weights and activations are both scaled by 2^24 before they are split: the
+// last bit of the smallest float, 2^-149, becomes 2^-125, so every non-zero
+// part of every value is a normal bf16 number and the split is exact over the
+// whole range (unscaled it ends at 2^-110, where l falls below the smallest
+// subnormal). The sums are scaled back, which is exact too.
 #pragma once
 
 #include <cmath>
@@ -33,10 +38,12 @@ inline void split3(float w, uint16_t part[3]) {
   part[2] = f2bf(r - bf2f(part[1]));
 }
 
-// Largest magnitude of a weight that is split. (h of one within half a bf16
-// unit of the largest float would round to infinity and m, l to minus
-// infinity and NaN; layers with larger, infinite or NaN weights run on the
-// fp32 matrix instruction.)
+constexpr float kSplitScale = 0x1p24f;
+
+// Largest magnitude of a weight that is split: scaled, its parts stay well
+// below the largest bf16 (h would round to infinity, m and l to minus infinity
+// and NaN). Layers with larger, infinite or NaN weights run on the fp32 matrix
+// instruction.
 constexpr float kSplitMax = 0x1p100f;
 inline bool splittable(float w) { return std::fabs(w) <= kSplitMax; }
 

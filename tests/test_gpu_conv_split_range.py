@@ -1,6 +1,7 @@
 """fp32 convolutions at the ends of the float range. Layers whose weights the
 three-way bf16 split cannot hold (near the largest float, infinite, NaN) give
-what the fp32 matrix instruction gives."""
+what the fp32 matrix instruction gives; tiny weights and activations keep
+their precision."""
 import numpy as np
 import pytest
 import torch
@@ -42,6 +43,30 @@ def test_extreme_weights(stride, transposed, cout, value):
         fits = terms < 3.4e38
         assert fits.any()
         assert np.all(np.abs(ref[0].astype(np.float64) - want)[fits] <= (2e-5 * terms + 1e-6)[fits])
+
+
+@pytest.mark.parametrize("stride,transposed,cout", LAYERS)
+@pytest.mark.parametrize("xs,ws", [(1e-30, 1.0), (1e-36, 1.0), (2e-37, 2.0 ** 60), (1.0, 1e-36), (2.0 ** 60, 2e-37),
+                                   (1e-17, 1e-18)])
+def test_tiny_values(stride, transposed, cout, xs, ws):
+    """No further from float64 than the fp32 matrix instruction (5 % for the
+    spread of a sample, as for ordinary magnitudes), and within fp32
+    accumulation over K terms of it."""
+    from paper_2112_10603_amd import op_conv
+    print(f"case fp32 tiny x {xs} w {ws} s={stride} T={transposed} cout={cout}", flush=True)
+    x, wt, b = _data(cout, transposed, 11)
+    x, wt, b = x * np.float32(xs), wt * np.float32(ws), np.zeros_like(b)
+    xd = torch.from_numpy(x).cuda()
+    kw = dict(stride=max(stride, 1), transposed=transposed, precision="fp32")
+    got = op_conv(xd, wt, b, **kw).cpu().numpy()[0].astype(np.float64)
+    plain = op_conv(xd, wt, b, n_tile=32, **kw).cpu().numpy()[0].astype(np.float64)
+    x64, w64, b64 = (v.astype(np.float64) for v in (x[0], wt, b))
+    conv = O.conv_transpose2d if transposed else (lambda p, q, r: O.conv2d(p, q, r, stride))
+    want, terms = conv(x64, w64, b64), conv(np.abs(x64), np.abs(w64), np.abs(b64))
+    e_got, e_plain = np.linalg.norm(got - want), np.linalg.norm(plain - want)
+    print(f"  error {e_got / np.linalg.norm(want):.2e} fp32 MFMA {e_plain / np.linalg.norm(want):.2e}")
+    assert e_got <= 1.05 * e_plain
+    assert np.all(np.abs(got - want) <= 2e-5 * terms)
 
 
 def test_net_with_extreme_weights(tmp_path):
