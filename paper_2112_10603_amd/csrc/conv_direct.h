@@ -25,8 +25,8 @@
 // that of v_mfma_f32_32x32x2f32: 2.2e-7 against 6.0e-7 relative (256
 // channels, 3x3). A tile that meets a value the split cannot hold (infinity,
 // NaN, or a magnitude past 2^104) or a sum past 2^80 gives a non-finite
-// accumulator; such a wave recomputes its outputs with plain fp32
-// multiply-adds. Layers with weights that the split cannot hold (split3.h)
+// accumulator; such a wave recomputes its outputs on the fp32 matrix
+// instruction. Layers with weights that the split cannot hold (split3.h)
 // have no weights in fragment order and run on the fp32 matrix instruction.
 //
 // What bounds it. Small grids: the chain of a workgroup's K rounds (144 for
@@ -460,33 +460,63 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void conv_direct(ConvArgs a, Dir
       for (int j = 0; j < FN; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) bad = bad || !(fabsf(acc[i][j][e]) <= 3.402823466e38f);
-    if (__any(bad)) {  // the wave's tile again, one fp32 multiply-add at a time
-      const uint16_t* wf = reinterpret_cast<const uint16_t*>(a.wfrag);
-      for (int t = lane; t < FM * 32 * FN * 32; t += 64) {
-        const int p = wm * FM * 32 + t / (FN * 32), n = n0 + wn * FN * 32 + t % (FN * 32);
-        const int oy = ty0 + p / TW, ox = tx0 + p % TW;
-        if (oy >= a.Ho || ox >= a.Wo || n >= a.n_rows) continue;
-        const uint16_t* ws = wf + ((long)phase * n32 + n / 32) * (stream / 2);
-        float sum = 0.f;
-        for (int st = 0; st < pl.slices * TAPS; ++st) {
-          const int slice = st / TAPS, tap = st - slice * TAPS;
-          const int dy = TAPS == 4 ? py - (tap >> 1) : tap / 3 - 1, dx = TAPS == 4 ? px - (tap & 1) : tap % 3 - 1;
-          const int iy = oy * ST + dy, ix = ox * ST + dx;
-          if (iy < 0 || iy >= a.Hi || ix < 0 || ix >= a.Wi) continue;
-          const float* x = reinterpret_cast<const float*>(in_img) + (long)(iy * a.Wi + ix) * a.in_ld + slice * BK;
-          for (int c = 0; c < BK && slice * BK + c < a.cin_pad; ++c) {
-            const int ch = c >> 2;  // chunk: lane half ch / 4, round (ch % 4) / 2
-            const uint16_t* wp = ws + (((st * 2 + ((ch & 3) >> 1)) * 3 * 64) + ((ch >> 2) << 5) + (n & 31)) * 8 +
-                                 (ch & 1) * 4 + (c & 3);
-            const float w = __uint_as_float((uint32_t)wp[0] << 16) + __uint_as_float((uint32_t)wp[512] << 16) +
-                            __uint_as_float((uint32_t)wp[1024] << 16);
-            sum = fmaf(x[c], w * (1.f / kSplitScale), sum);
+    if (__any(bad)) {
+      // The wave's tile again from unsplit operands on the fp32 matrix
+      // instruction, K in the same order, read from global memory (the halo
+      // ring may hold later slices only). One loop, so that it takes no
+      // registers from the ordinary path. (A view of 192 x 256 whose images
+      // are infinite: 62.9 ms with one multiply-add per lane at a time, 1.85
+      // so; 0.83 for ordinary images.)
+      const float* x = reinterpret_cast<const float*>(in_img);
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      const char* ws = reinterpret_cast<const char*>(a.wfrag) + ((long)phase * n32 + n0 / 32 + wn * FN) * stream + lane16;
+#pragma unroll 1
+      for (int k = 0; k < pl.slices * U; ++k) {
+        const int st = k / R, slice = st / TAPS, tap = st - slice * TAPS;
+        const int dy = TAPS == 4 ? py - (tap >> 1) : tap / 3 - 1, dx = TAPS == 4 ? px - (tap & 1) : tap % 3 - 1;
+        const int c = slice * BK + lhalf * 16 + (k - st * R) * 8;
+        float4 v[FM][2];
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+          const int p = (wm * FM + i) * 32 + lrow, ry = p / TW;
+          const int iy = (ty0 + ry) * ST + dy, ix = (tx0 + p - ry * TW) * ST + dx;
+          v[i][0] = v[i][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (iy >= 0 && iy < a.Hi && ix >= 0 && ix < a.Wi && c < a.cin_pad) {
+            const float4* src = reinterpret_cast<const float4*>(x + (long)(iy * a.Wi + ix) * a.in_ld + c);
+            v[i][0] = src[0];
+            v[i][1] = src[1];
           }
         }
-        const long pix = img_off + ((long)((oy << sh) + py) * a.Wout + (ox << sh) + px) * a.out_ld;
-        store_col(pix, n, sum);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          uint4 part[3];
+#pragma unroll
+          for (int l = 0; l < 3; ++l) part[l] = *reinterpret_cast<const uint4*>(ws + j * stream + (long)(k * 3 + l) * 1024);
+          float w[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            float sum = 0.f;
+#pragma unroll
+            for (int l = 0; l < 3; ++l) {
+              const uint32_t d = reinterpret_cast<const uint32_t*>(&part[l])[e >> 1];
+              sum += __uint_as_float(e & 1 ? d & 0xffff0000u : d << 16);
+            }
+            w[e] = sum * (1.f / kSplitScale);
+          }
+#pragma unroll
+          for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              mfma_chunk<float>(acc[i][j], make_uint4(__float_as_uint(w[4 * h]), __float_as_uint(w[4 * h + 1]),
+                                                      __float_as_uint(w[4 * h + 2]), __float_as_uint(w[4 * h + 3])),
+                                __builtin_bit_cast(uint4, v[i][h]));
+        }
       }
-      return;
     }
   }
 
