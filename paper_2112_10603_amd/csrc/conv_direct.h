@@ -25,9 +25,9 @@
 // that of v_mfma_f32_32x32x2f32: 2.2e-7 against 6.0e-7 relative (256
 // channels, 3x3). A tile that meets a value the split cannot hold (infinity,
 // NaN, or a magnitude past 2^104) or a sum past 2^80 gives a non-finite
-// accumulator; such a wave recomputes its outputs on the fp32 matrix
-// instruction. Layers with weights that the split cannot hold (split3.h)
-// have no weights in fragment order and run on the fp32 matrix instruction.
+// accumulator; such outputs are recomputed on the fp32 matrix instruction.
+// Layers with weights that the split cannot hold (split3.h) have no weights in
+// fragment order and run on the fp32 matrix instruction.
 //
 // What bounds it. Small grids: the chain of a workgroup's K rounds (144 for
 // 256 channels): dependent MFMAs are 64 cycles apart, 3.8 us in all, and about
@@ -453,27 +453,31 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void conv_direct(ConvArgs a, Dir
       for (int j = 0; j < FN; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] *= unscale;
+    auto is_bad = [&](float v) { return !(fabsf(v) <= 3.402823466e38f); };
     bool bad = false;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
       for (int j = 0; j < FN; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) bad = bad || !(fabsf(acc[i][j][e]) <= 3.402823466e38f);
+        for (int e = 0; e < 16; ++e) bad = bad || is_bad(acc[i][j][e]);
     if (__any(bad)) {
       // The wave's tile again from unsplit operands on the fp32 matrix
       // instruction, K in the same order, read from global memory (the halo
-      // ring may hold later slices only). One loop, so that it takes no
-      // registers from the ordinary path. (A view of 192 x 256 whose images
+      // ring may hold later slices only), for the outputs that are not finite;
+      // the others keep their sums, so that an output does not depend on which
+      // others share its wave, i.e. on the launch's tile. One loop, so that it
+      // takes no registers from the ordinary path. (A view of 192 x 256 whose images
       // are infinite: 62.9 ms with one multiply-add per lane at a time, 1.85
       // so; 0.83 for ordinary images.)
       const float* x = reinterpret_cast<const float*>(in_img);
+      f32x16 re[FM][FN];
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+          for (int e = 0; e < 16; ++e) re[i][j][e] = 0.f;
       const char* ws = reinterpret_cast<const char*>(a.wfrag) + ((long)phase * n32 + n0 / 32 + wn * FN) * stream + lane16;
 #pragma unroll 1
       for (int k = 0; k < pl.slices * U; ++k) {
@@ -512,11 +516,18 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void conv_direct(ConvArgs a, Dir
           for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-              mfma_chunk<float>(acc[i][j], make_uint4(__float_as_uint(w[4 * h]), __float_as_uint(w[4 * h + 1]),
+              mfma_chunk<float>(re[i][j], make_uint4(__float_as_uint(w[4 * h]), __float_as_uint(w[4 * h + 1]),
                                                       __float_as_uint(w[4 * h + 2]), __float_as_uint(w[4 * h + 3])),
                                 __builtin_bit_cast(uint4, v[i][h]));
         }
       }
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if (is_bad(acc[i][j][e])) acc[i][j][e] = re[i][j][e];
     }
   }
 
