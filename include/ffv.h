@@ -43,9 +43,10 @@ typedef enum {
 } ffv_status;
 
 typedef enum {
-  FFV_FP32 = 0,      /* fp32 activations and accumulation; every product of a
-                        convolution exact to below 2^-26 (operands split into three
-                        bf16 parts for the matrix cores) */
+  FFV_FP32 = 0,      /* fp32 activations and accumulation; a convolution's operands
+                        are split exactly into three bf16 parts for the matrix
+                        cores, each product within 2^-24 + 2^-34 of itself (the
+                        rounding of an fp32 multiplication) */
   FFV_BF16 = 1,      /* convolutions on bf16 MFMA with fp32 accumulation */
   FFV_FP8_E4M3 = 2   /* VIBlock 128/256-channel convs in fp8 e4m3 (per-channel activation
                         scales folded into per-output-channel weight scales, fp32

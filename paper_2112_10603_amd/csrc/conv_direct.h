@@ -18,9 +18,10 @@
 // fp32 layers run on the bf16 matrix cores: every fp32 operand is scaled (see
 // split3.h) and split exactly into three bf16 parts, x = h + m + l (8 + 8 + 8
 // significand bits, each the rest rounded to nearest), activations in
-// registers, weights when they are packed, and the six products of weight 2^-16 and more are summed:
-// h*h in one fp32 accumulator, h*m, m*h, m*m, h*l, l*h in another, added at
-// the end. The dropped products are below 2^-26 of h*h. Rounding once per 16
+// registers, weights when they are packed, and the six largest products are
+// summed: h*h in one fp32 accumulator, h*m, m*h, m*m, h*l, l*h in another,
+// added at the end. The three dropped ones are at most 2^-24 + 2^-34 of x*w,
+// one rounding of an fp32 product (split3.h). Rounding once per 16
 // products instead of once per 2, the error against float64 is smaller than
 // that of v_mfma_f32_32x32x2f32: 2.2e-7 against 6.0e-7 relative (256
 // channels, 3x3). A tile that meets a value the split cannot hold (infinity,

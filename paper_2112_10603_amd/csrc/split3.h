@@ -45,6 +45,13 @@ constexpr float kSplitScale = 0x1p24f;
 // and NaN). Layers with larger, infinite or NaN weights run on the fp32 matrix
 // instruction.
 constexpr float kSplitMax = 0x1p100f;
+
+// A product x w is summed as its six largest part products. |m| <= 2^-8 |x|
+// and |l| <= 2^-17 |x|, so the dropped m l, l m and l l are at most 2^-24 +
+// 2^-34 of it: one rounding of an fp32 multiplication, reached by x = w =
+// 1 + 2^-8 - 2^-17. (m l and l m too would be a third more matrix work.)
+constexpr double kSplitProductError = 0x1.004p-24;
+
 inline bool splittable(float w) { return std::fabs(w) <= kSplitMax; }
 
 }  // namespace ffv
