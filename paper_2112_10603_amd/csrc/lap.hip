@@ -27,10 +27,10 @@
 // 3 x 3 coarse samples serve four fine ones, and the four signs are stored
 // as one byte.
 //
-// Reductions: each workgroup of the band pass reduces |L| of its samples in
-// fp32 across the wavefront and the workgroup, and writes one double
-// partial; one workgroup per image sums them in a fixed order in double, so
-// the result does not depend on scheduling.
+// Reductions: each workgroup of the band pass sums |L| of its samples in
+// double (an fp32 sum of a quad already loses a row 2^-23 times as large as
+// its neighbour) and writes one partial; one workgroup per image sums them in
+// a fixed order in double, so the result does not depend on scheduling.
 //
 // Measured (one MI355X, whole call): 8 x 3 x 256 x 448 with gradient 561 ->
 // 84 us, 1 x 3 x 1079 x 1917 without 2632 -> 73 us. (The bands formed in the
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(TPB) void band_k(BandArgs t) {
   const long plane = blockIdx.y;
   const int h = t.L.h[l], w = t.L.w[l], hn = t.L.h[l + 1], wn = t.L.w[l + 1];
   const int q = ((int)blockIdx.x - t.first[l]) * TPB + threadIdx.x;
-  float sum = 0.f;
+  double sum = 0.0;
   if (q < hn * wn) {
     const int yq = q / wn, xq = q - yq * wn;
     const float* g = t.G[l + 1] + plane * hn * wn;
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(TPB) void band_k(BandArgs t) {
       float v = a[o];
       if (l == 0) v -= t.gt[o];
       const float band = v - 4.f * acc;
-      sum += fabsf(band);
+      sum += (double)fabsf(band);
       signs |= (band > 0.f ? 1u : (band < 0.f ? 2u : 0u)) << (2 * k);
     }
     if (t.S[l]) t.S[l][plane * hn * wn + q] = (uint8_t)signs;
@@ -251,13 +251,13 @@ __global__ __launch_bounds__(TPB) void band_k(BandArgs t) {
   // wavefront reduction, then the workgroup's four wavefronts
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  __shared__ float wsum[TPB / 64];
+  __shared__ double wsum[TPB / 64];
   if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = sum;
   __syncthreads();
   if (threadIdx.x == 0) {
     double s = 0.0;
 #pragma unroll
-    for (int i = 0; i < TPB / 64; ++i) s += (double)wsum[i];
+    for (int i = 0; i < TPB / 64; ++i) s += wsum[i];
     t.partial[plane * gridDim.x + blockIdx.x] = t.weight[l] * s;
   }
 }
