@@ -140,13 +140,13 @@ ffv_status ffv_interpolate_recursive(ffv_net* net, const ffv_pair* views, int32_
  * variants with 128/64/32; the 256 pixels form a tile_w-wide 2-D block). Runs the call exactly as ffv_interpolate does (same arguments, same
  * result in *out*), then re-launches each convolution of that call with
  * every candidate (N tile at most twice the real channel count rounded to
- * 32; pixel-block widths 8, 16, 32, 64 within 10 % of the least padding),
- * timed with HIP events on the net's stream, and keeps the fastest per
+ * 32; pixel-block widths 8, 16, 32, 64 within 10 % of the least padding; the
+ * direct-weight kernel where it is the default, i.e. on small grids), timed with HIP events on the net's stream, and keeps the fastest per
  * (layer, fp8 or not, output grid, images per launch). Later calls whose
  * launches match use those choices; captured graphs are dropped.
- * Launches of the direct-weight kernel (small grids, and every fp32 layer)
- * have nothing to choose: they get an entry that names their default tile,
- * and run that kernel whatever the table says.
+ * fp32 layers have nothing to choose (their direct-weight tiles differ from
+ * the others in the order of their sums): they get an entry that names it,
+ * and run it whatever the table says.
  * *n_tuned (nullable) = launch shapes tuned. Takes seconds at 1080p batch
  * sizes. Errors as ffv_interpolate.
  */
@@ -155,11 +155,14 @@ ffv_status ffv_autotune(ffv_net* net, const ffv_pair* views, int32_t n_pairs, co
 
 /*
  * Tuning table as text, one line per launch shape:
- * "layer fp8 Ho Wo n_img n_tile tile_w" ('#' starts a comment line); n_tile
+ * "layer fp8 Ho Wo n_img n_tile tile_w vs_direct" ('#' starts a comment line); n_tile
  * is 256, 128, 64, 32, or h256, h128, h32 for the halo variants, r64, r32
  * for the resident-weight variants, s128, s64, s32 for the few-channel ones,
  * q256 for the 2 x 4-wave halo tile, p256 for the halo tile whose two wave
- * groups alternate MFMA and memory phases.
+ * groups alternate MFMA and memory phases, direct for the direct-weight
+ * kernel. vs_direct (may be missing: 0) = 1 when the direct-weight kernel was
+ * among the candidates: other entries leave that kernel where it is the
+ * default.
  * ffv_save_tuning writes the net's table; ffv_load_tuning merges a file's
  * entries into it (*n_loaded, nullable, = entries read) and rejects the
  * whole file on a malformed line, an unknown layer or a tile that does not

@@ -89,10 +89,12 @@ struct ConvGroup {
 // width 16); Q256: the 256-column halo tile with its waves as 2 x 4 (on a
 // per-phase transposed conv with at most 64 outputs, all four phases in one
 // workgroup); P256: the H256 tile with its eight waves in two groups whose
-// MFMA and memory phases alternate (same results bit for bit).
+// MFMA and memory phases alternate (same results bit for bit); D, in tuning
+// tables only: the direct-weight kernel on the tile of its own rule
+// (conv_direct_tile).
 enum class ConvTile : int {
   N256 = 0, N128 = 1, N64 = 2, N32 = 3, H32 = 4, H256 = 5, H128 = 6, R32 = 7, R64 = 8, S32 = 9, S64 = 10, S128 = 11,
-  Q256 = 12, P256 = 13
+  Q256 = 12, P256 = 13, D = 14
 };
 // N tile (output channels per workgroup) of a tile kind.
 inline int conv_tile_bn(ConvTile t) {

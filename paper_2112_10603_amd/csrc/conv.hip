@@ -73,6 +73,8 @@ hipError_t launch_t(ConvTile tile, const ConvArgs* g, int n, hipStream_t s) {
       return launch_s2<T, 64>(g[0], s);
     case ConvTile::S128:
       return launch_s2<T, 128>(g[0], s);
+    case ConvTile::D:  // launch_conv_direct runs it
+      break;
   }
   return hipErrorInvalidValue;
 }

@@ -744,22 +744,37 @@ Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long 
   a.taps = L.mode == 1 ? 4 : 9;
   a.zero = zero_;
   const DType kdt = in_fp8 ? DType::FP8 : dt_;
-  ConvTile tile = L.tile;
-  // small grids, and every fp32 layer: the direct-weight kernel (whatever the
-  // tuning table says: the table chooses among the other tiles)
-  int direct_w = 0;
-  const DirectTile direct = conv_direct_tile(kdt, a, &direct_w);
-  auto pick = [&](const ConvArgs& c, ConvTile* t, int* tw) {  // the rule's tile, or the table's
-    default_tile(kdt, c, L.tile, t, tw);
-    auto it = tuned_.find(TuneKey{L.name, in_fp8 ? 1 : 0, c.Ho, c.Wo, c.n_img});
-    if (it != tuned_.end()) {
-      *t = it->second.tile;
-      *tw = it->second.tile_w;
-    }
+  // The table's choice, else the rules': the direct-weight kernel on small
+  // grids and for fp32 layers, default_tile() beyond. A table entry that was
+  // not timed against the direct kernel chooses among the other tiles only,
+  // as does every entry of an fp32 layer (the direct kernel's sums differ from
+  // the other tiles', and a view must not depend on its batch).
+  struct Choice {
+    DirectTile direct;
+    ConvTile tile;
+    int tile_w;
   };
-  pick(a, &tile, &a.tile_w);
-  if (recording_)
-    recs_.push_back(TuneRec{TuneKey{L.name, in_fp8 ? 1 : 0, a.Ho, a.Wo, n_img}, a, kdt, direct != DirectTile::None});
+  auto pick = [&](const ConvArgs& c) {
+    Choice p{};
+    int direct_w = 0;
+    p.direct = conv_direct_tile(kdt, c, &direct_w);
+    default_tile(kdt, c, L.tile, &p.tile, &p.tile_w);
+    auto it = tuned_.find(TuneKey{L.name, in_fp8 ? 1 : 0, c.Ho, c.Wo, c.n_img});
+    if (it != tuned_.end() && it->second.tile != ConvTile::D) {
+      p.tile = it->second.tile;
+      p.tile_w = it->second.tile_w;
+      if (it->second.vs_direct && kdt != DType::F32) p.direct = DirectTile::None;
+    }
+    if (p.direct != DirectTile::None) p.tile_w = direct_w;
+    return p;
+  };
+  const Choice choice = pick(a);
+  a.tile_w = choice.tile_w;
+  if (recording_) {
+    int direct_w = 0;
+    const DirectTile direct = conv_direct_tile(kdt, a, &direct_w);
+    recs_.push_back(TuneRec{TuneKey{L.name, in_fp8 ? 1 : 0, a.Ho, a.Wo, n_img}, a, kdt, direct, direct_w});
+  }
   if (in_ld < L.cin_pad || in_ld % (in_fp8 ? 16 : 8) != 0) return Status::err(-4, "conv input stride");
   if ((in_fp8 && !L.w8_dev) || (out_fp8 && !L.out_scale)) return Status::err(-7, "fp8 layer not quantised");
   const double flops = 2.0 * n_img * (double)a.Hout * a.Wout * L.cout * L.cin *
@@ -813,15 +828,14 @@ Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long 
     ConvTile gt[ConvGroup::kMax];
     bool done[ConvGroup::kMax] = {};
     for (int j = 0; j < x.n_groups && st.good(); ++j) {
-      int tw = 0;
-      const DirectTile d = conv_direct_tile(kdt, g[j], &tw);
-      pick(g[j], &gt[j], &g[j].tile_w);
-      if (d != DirectTile::None) g[j].tile_w = tw;
-      done[j] = d != DirectTile::None || !conv_tile_groupable(gt[j]);
-      if (d != DirectTile::None)
-        st = check(launch_conv_direct(kdt, d, g[j], x.s), L.name.c_str());
+      const Choice c = pick(g[j]);
+      gt[j] = c.tile;
+      g[j].tile_w = c.tile_w;
+      done[j] = c.direct != DirectTile::None || !conv_tile_groupable(c.tile);
+      if (c.direct != DirectTile::None)
+        st = check(launch_conv_direct(kdt, c.direct, g[j], x.s), L.name.c_str());
       else if (done[j])
-        st = check(launch_conv(kdt, gt[j], g[j], x.s), L.name.c_str());
+        st = check(launch_conv(kdt, c.tile, g[j], x.s), L.name.c_str());
     }
     for (int j = 0; j < x.n_groups && st.good(); ++j) {
       if (done[j]) continue;
@@ -838,13 +852,9 @@ Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long 
     return st;
   }
   prof_begin(x);
-  Status st;
-  if (direct != DirectTile::None) {
-    a.tile_w = direct_w;
-    st = check(launch_conv_direct(kdt, direct, a, x.s), L.name.c_str());
-  } else {
-    st = check(launch_conv(kdt, tile, a, x.s), L.name.c_str());
-  }
+  const Status st = check(choice.direct != DirectTile::None ? launch_conv_direct(kdt, choice.direct, a, x.s)
+                                                            : launch_conv(kdt, choice.tile, a, x.s),
+                          L.name.c_str());
   prof_end(x, cls, flops);
   return st;
 }
@@ -1466,8 +1476,8 @@ Status Net::autotune(const float* const* left, const float* const* right, int n_
   for (size_t r = 0; res.good() && r < recs_.size(); ++r) {
     const TuneRec& rec = recs_[r];
     if (found.count(rec.key)) continue;
-    if (rec.direct) {
-      found[rec.key] = TuneVal{layers_.at(rec.key.layer).tile, rec.a.tile_w};
+    if (rec.direct != DirectTile::None && rec.dt == DType::F32) {  // nothing to choose
+      found[rec.key] = TuneVal{ConvTile::D, rec.direct_w, true};
       continue;
     }
     const int rows32 = round_up(rec.a.n_rows, 32);
@@ -1479,6 +1489,35 @@ Status Net::autotune(const float* const* left, const float* const* right, int n_
     }
     float best_ms = -1.f;
     TuneVal best{};
+    const bool direct = rec.direct != DirectTile::None;
+    // Time of one launch: two in a row after a warm-up, ten more when they
+    // are short (there the event's own spread is as large as the differences).
+    auto time_tile = [&](ConvTile tile, int tw) -> Status {
+      ConvArgs a = rec.a;
+      a.tile_w = tw;
+      a.amax = nullptr;
+      auto launch = [&]() {
+        return tile == ConvTile::D ? launch_conv_direct(rec.dt, rec.direct, a, stream_)
+                                   : launch_conv(rec.dt, tile, a, stream_);
+      };
+      FFV_TRY(check(launch(), "autotune warm-up"));
+      float ms = 0.f;
+      for (int reps : {2, 10}) {
+        FFV_TRY(check(hipEventRecord(e0, stream_), "hipEventRecord"));
+        for (int k = 0; k < reps; ++k) FFV_TRY(check(launch(), "autotune launch"));
+        FFV_TRY(check(hipEventRecord(e1, stream_), "hipEventRecord"));
+        FFV_TRY(check(hipEventSynchronize(e1), "hipEventSynchronize"));
+        FFV_TRY(check(hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime"));
+        ms /= reps;
+        if (ms > 0.1f) break;
+      }
+      if (best_ms < 0.f || ms < best_ms) {
+        best_ms = ms;
+        best = TuneVal{tile, tw, direct};
+      }
+      return Status::ok();
+    };
+    if (direct) res = time_tile(ConvTile::D, rec.direct_w);
     for (int ti = 0; res.good() && ti < 14; ++ti) {
       const bool resident = tiles[ti] == ConvTile::R32 || tiles[ti] == ConvTile::R64;
       const bool s2 = tiles[ti] == ConvTile::S32 || tiles[ti] == ConvTile::S64 || tiles[ti] == ConvTile::S128;
@@ -1506,23 +1545,8 @@ Status Net::autotune(const float* const* left, const float* const* right, int n_
         ConvArgs a = rec.a;
         a.tile_w = tw;
         if (halo_big && !conv_halo_tile_ok(rec.dt, a)) continue;
-        a.amax = nullptr;
-        res = check(launch_conv(rec.dt, tiles[ti], a, stream_), "autotune warm-up");
+        res = time_tile(tiles[ti], tw);
         if (!res.good()) break;
-        res = check(hipEventRecord(e0, stream_), "hipEventRecord");
-        const int reps = 2;
-        for (int k = 0; res.good() && k < reps; ++k)
-          res = check(launch_conv(rec.dt, tiles[ti], a, stream_), "autotune launch");
-        if (res.good()) res = check(hipEventRecord(e1, stream_), "hipEventRecord");
-        if (res.good()) res = check(hipEventSynchronize(e1), "hipEventSynchronize");
-        float ms = 0.f;
-        if (res.good()) res = check(hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime");
-        if (!res.good()) break;
-        ms /= reps;
-        if (best_ms < 0.f || ms < best_ms) {
-          best_ms = ms;
-          best = TuneVal{tiles[ti], tw};
-        }
       }
     }
     if (res.good() && best_ms >= 0.f) found[rec.key] = best;
@@ -1544,6 +1568,7 @@ static std::string tile_name(ConvTile t) {
   if (t == ConvTile::S32 || t == ConvTile::S64 || t == ConvTile::S128) return "s" + n;
   if (t == ConvTile::Q256) return "q256";
   if (t == ConvTile::P256) return "p256";
+  if (t == ConvTile::D) return "direct";
   return (t == ConvTile::H32 || t == ConvTile::H256 || t == ConvTile::H128) ? "h" + n : n;
 }
 
@@ -1551,10 +1576,11 @@ Status Net::save_tuning(const std::string& path) {
   std::lock_guard<std::mutex> lk(call_mu_);
   FILE* f = std::fopen(path.c_str(), "w");
   if (!f) return Status::err(-1, "cannot open " + path + " for writing");
-  std::fprintf(f, "# ffv conv tuning v1: layer fp8 Ho Wo n_img n_tile tile_w\n");
+  std::fprintf(f, "# ffv conv tuning v2: layer fp8 Ho Wo n_img n_tile tile_w vs_direct\n");
   for (auto& kv : tuned_)
-    std::fprintf(f, "%s %d %d %d %d %s %d\n", kv.first.layer.c_str(), kv.first.fp8, kv.first.Ho,
-                 kv.first.Wo, kv.first.n_img, tile_name(kv.second.tile).c_str(), kv.second.tile_w);
+    std::fprintf(f, "%s %d %d %d %d %s %d %d\n", kv.first.layer.c_str(), kv.first.fp8, kv.first.Ho,
+                 kv.first.Wo, kv.first.n_img, tile_name(kv.second.tile).c_str(), kv.second.tile_w,
+                 kv.second.vs_direct ? 1 : 0);
   const bool ok = std::fclose(f) == 0;
   return ok ? Status::ok() : Status::err(-1, "write failed: " + path);
 }
@@ -1573,8 +1599,8 @@ Status Net::load_tuning(const std::string& path, int* n_loaded) {
     ++lineno;
     if (line[0] == '#' || line[0] == '\n') continue;
     char name[256], tname[16];
-    int fp8, ho, wo, n, tw;
-    if (std::sscanf(line, "%255s %d %d %d %d %15s %d", name, &fp8, &ho, &wo, &n, tname, &tw) != 7 ||
+    int fp8, ho, wo, n, tw, vs_direct = 0;
+    if (std::sscanf(line, "%255s %d %d %d %d %15s %d %d", name, &fp8, &ho, &wo, &n, tname, &tw, &vs_direct) < 7 ||
         (fp8 != 0 && fp8 != 1) || ho <= 0 || wo <= 0 || n <= 0 || tw <= 0 || tw > 256 || 256 % tw != 0 ||
         !layers_.count(name)) {
       st = Status::err(-1, path + ": bad entry on line " + std::to_string(lineno));
@@ -1596,6 +1622,7 @@ Status Net::load_tuning(const std::string& path, int* n_loaded) {
     else if (tn == "s32" && tw == 16) t = ConvTile::S32;
     else if (tn == "s64" && tw == 16) t = ConvTile::S64;
     else if (tn == "s128" && tw == 16) t = ConvTile::S128;
+    else if (tn == "direct") t = ConvTile::D;
     else {
       st = Status::err(-1, path + ": bad tile on line " + std::to_string(lineno));
       break;
@@ -1606,7 +1633,7 @@ Status Net::load_tuning(const std::string& path, int* n_loaded) {
       st = Status::err(-1, path + ": entry on line " + std::to_string(lineno) + " does not fit its layer");
       break;
     }
-    got[TuneKey{name, fp8, ho, wo, n}] = TuneVal{t, tw};
+    got[TuneKey{name, fp8, ho, wo, n}] = TuneVal{t, tw, vs_direct != 0};
   }
   std::fclose(f);
   FFV_TRY(st);

@@ -263,6 +263,7 @@ class Net {
   struct TuneVal {
     ConvTile tile;
     int tile_w;
+    bool vs_direct;  // timed against the direct-weight kernel too
   };
   std::map<TuneKey, TuneVal> tuned_;
   bool recording_ = false;  // conv() records its launches for autotune()
@@ -270,7 +271,8 @@ class Net {
     TuneKey key;
     ConvArgs a;
     DType dt;
-    bool direct;  // the direct kernel runs it: nothing to tune
+    DirectTile direct;  // the direct-weight kernel's tile, or None
+    int direct_w;
   };
   std::vector<TuneRec> recs_;
 
