@@ -345,9 +345,10 @@ ffv_status ffv_stitch_cluster(const float* real_view, const float* const* left,
  * precision: FFV_FP32 or FFV_BF16 (inputs and weights rounded to bf16, fp32
  * accumulation and output), optionally or'ed with FFV_OP_ACT_OUT: the layer
  * writes its output in the activation dtype (bf16 for FFV_BF16), as the
- * network's layers do, and y receives those values widened to float32. n_tile (0 = the layer's default,
- * which with tile_w = 0 is the tile the network would take, the direct-weight
- * kernel included; else 256, 128, 64 or 32 output channels per workgroup, or 1 = the halo-reuse kernel:
+ * network's layers do, and y receives those values widened to float32. n_tile (0 = the layer's
+ * default, which with tile_w = 0 is the tile that the network takes for the
+ * same launch without a tuning table, the direct-weight kernel included where
+ * its weights are at most 32 MiB; else 256, 128, 64 or 32 output channels per workgroup, or 1 = the halo-reuse kernel:
  * 32 channels of a 16x16 pixel block, for stride-1 convs whose input
  * channels are a multiple of the K step; 2 and 3 = the 128- and 256-channel
  * tiles reading each channel slice's input halo once, for stride-1 and
@@ -409,7 +410,8 @@ ffv_status ffv_lap_loss(const float* x, const float* gt, int32_t n, int32_t heig
  * ffv_op_conv, and it runs the same kernels, so the two give the same
  * values bit for bit. Its device buffers (NHWC input copy, packed weights,
  * bias, NHWC output, zero block, each rounded up to 256 bytes) live in one
- * array of FFV_OP_NOALLOC_SCRATCH_BYTES per device, which the library holds
+ * array of FFV_OP_NOALLOC_SCRATCH_BYTES per device (and another of 32 MiB, for
+ * the weights of the direct-weight kernel), which the library holds
  * from the first call on that device until the process ends. A layer whose
  * buffers do not fit is rejected with FFV_ERR_ARG before any device work.
  * The call works on the current device, orders its work on `stream`

@@ -434,45 +434,43 @@ ffv_status op_conv_run(const OpConvScratch* scratch, int32_t precision, const fl
   a.accumulate = 0;
   a.taps = L.mode == 1 ? 4 : 9;
   a.tile_w = tile_w > 0 ? tile_w : conv_tile_width(a.Ho, a.Wo);
+  // The default tile as the network chooses it
+  ConvTile tile = L.tile;
+  DirectTile direct = DirectTile::None;
+  if (n_tile == 0 && tile_w == 0) {
+    int tw = 0;
+    if (direct_layer(L, dt) && direct_bytes(L, dt) <= kOpDirectBytes) {
+      a.wfrag = x;  // any non-null pointer: only the shape counts here
+      direct = conv_direct_tile(dt, a, &tw);
+      a.wfrag = nullptr;
+    }
+    if (direct != DirectTile::None)
+      a.tile_w = tw;
+    else
+      conv_default_tile(dt, a, L.tile, &tile, &a.tile_w);
+  }
+  const size_t packed_bytes = (size_t)(L.mode == 1 ? 4 : 1) * L.cout_pad * L.K_pad * e;
+  const std::vector<uint8_t> packed = direct == DirectTile::None ? pack_layer(L, dt) : pack_direct(L, dt);
   // the call's device buffers: NHWC input, packed weights, bias, NHWC output
   // and a zero block for taps outside the image
-  size_t sizes[5] = {(size_t)n * h * w * L.cin_pad * e, 0, (size_t)cout * 4,
-                     (size_t)n * ho * wo * cout * dtype_size(out_dt), 256};
-  auto need_with = [&](size_t weights) {
-    size_t need = (weights + 255) / 256 * 256;
-    for (size_t b : sizes) need += (b + 255) / 256 * 256;
-    return need;
-  };
-  // The default tile as the network chooses it: the direct-weight kernel
-  // where it takes the launch and its larger weights fit the no-allocation
-  // entry point's scratch too (so that both entry points give the same bits).
-  DirectTile direct = DirectTile::None;
-  std::vector<uint8_t> packed;
-  if (n_tile == 0 && tile_w == 0 && direct_layer(L, dt)) {
-    a.wfrag = x;  // any non-null pointer: only the shape counts here
-    int tw = 0;
-    direct = conv_direct_tile(dt, a, &tw);
-    a.wfrag = nullptr;
-    if (direct != DirectTile::None) {
-      packed = pack_direct(L, dt);
-      if (need_with(packed.size()) <= FFV_OP_NOALLOC_SCRATCH_BYTES)
-        a.tile_w = tw;
-      else
-        direct = DirectTile::None;
-    }
-  }
-  if (direct == DirectTile::None) packed = pack_layer(L, dt);
-  sizes[1] = packed.size();
+  const size_t sizes[5] = {(size_t)n * h * w * L.cin_pad * e, packed.size(), (size_t)cout * 4,
+                           (size_t)n * ho * wo * cout * dtype_size(out_dt), 256};
   void* buf[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   hipError_t err = hipSuccess;
   if (scratch) {
+    // (a layer fits or not whatever the kernel: the direct kernel's weights
+    // have their own array)
     size_t need = 0;
-    for (size_t b : sizes) need += (b + 255) / 256 * 256;
+    for (int i = 0; i < 5; ++i) need += ((i == 1 ? packed_bytes : sizes[i]) + 255) / 256 * 256;
     if (need > scratch->cap)
       return fail(FFV_ERR_ARG, "layer needs " + std::to_string(need) + " bytes of scratch; the no-allocation "
                                "entry point holds " + std::to_string(scratch->cap));
     char* p = static_cast<char*>(scratch->base);
     for (int i = 0; i < 5; ++i) {
+      if (i == 1 && direct != DirectTile::None) {
+        buf[i] = scratch->direct;
+        continue;
+      }
       buf[i] = p;
       p += (sizes[i] + 255) / 256 * 256;
     }
@@ -498,7 +496,6 @@ ffv_status op_conv_run(const OpConvScratch* scratch, int32_t precision, const fl
     a.bias = (const float*)bd;
     a.out = yo;
     a.zero = zr;
-    ConvTile tile = L.tile;
     if (n_tile == 256) tile = ConvTile::N256;
     if (n_tile == 128) tile = ConvTile::N128;
     if (n_tile == 64) tile = ConvTile::N64;

@@ -137,6 +137,11 @@ hipError_t launch_direct_f8(DirectTile tile, const ConvArgs& a, hipStream_t s);
 // loads may run ahead into (contents unused).
 constexpr size_t kDirectPad = 64 << 10;
 
+// Tile and pixel block width of a launch without a tuning entry that is not of
+// the direct-weight kernel; narrowest: the narrowest generic tile that holds
+// the layer.
+void conv_default_tile(DType dt, const ConvArgs& a, ConvTile narrowest, ConvTile* tile, int* tile_w);
+
 hipError_t launch_conv(DType dt, ConvTile tile, const ConvArgs& a, hipStream_t s);
 // One launch over n (1 .. ConvGroup::kMax) groups of images of the same
 // layer; with more than one group only the generic tiles (N*) and the

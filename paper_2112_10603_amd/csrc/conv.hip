@@ -104,6 +104,25 @@ bool direct_fits(DType dt, const ConvArgs& a, DirectTile tile) {
                           : (dt == DType::BF16 ? direct_fits_t<bf16>(a, tile) : direct_fits_t<f8>(a, tile));
 }
 
+// Block width (32, 16 or 8) of the halo tiles with the least padded area for
+// a launch, or 0 when the halo tiles cannot run it.
+int halo_default_width(DType dt, const ConvArgs& a0) {
+  int best = 0;
+  long best_area = -1;
+  for (int tw : {32, 16, 8}) {
+    ConvArgs a = a0;
+    a.tile_w = tw;
+    if (!conv_halo_tile_ok(dt, a)) continue;
+    const int th = 256 / tw;
+    const long area = (long)((a.Ho + th - 1) / th) * th * ((a.Wo + tw - 1) / tw) * tw;
+    if (best_area < 0 || area < best_area) {
+      best_area = area;
+      best = tw;
+    }
+  }
+  return best;
+}
+
 }  // namespace
 
 int conv_k_step(DType dt) { return dt == DType::F32 ? 32 : (dt == DType::BF16 ? 64 : 128); }
@@ -254,6 +273,61 @@ hipError_t launch_conv_direct(DType dt, DirectTile tile, const ConvArgs& a, hipS
   if (a.n_img <= 0 || a.Ho <= 0 || a.Wo <= 0) return hipSuccess;
   if (dt == DType::F32) return launch_direct_f32(tile, a, s);
   return dt == DType::FP8 ? launch_direct_f8(tile, a, s) : launch_direct_bf16(tile, a, s);
+}
+
+// The figures are us per launch, one MI355X.
+void conv_default_tile(DType kdt, const ConvArgs& a, ConvTile narrowest, ConvTile* tile, int* tile_w) {
+  const int rows = a.n_rows;
+  *tile = narrowest;  // the narrowest generic tile that holds the layer
+  *tile_w = conv_tile_width(a.Ho, a.Wo);
+  const bool matrix16 = kdt != DType::F32;
+  const int hw = matrix16 ? halo_default_width(kdt, a) : 0;  // 0: no halo tile runs it
+  auto m_tiles = [&](int tw) {
+    const int th = 256 / tw;
+    return (long)a.n_img * ((a.Ho + th - 1) / th) * ((a.Wo + tw - 1) / tw);
+  };
+  auto use = [&](ConvTile t, int tw) {
+    *tile = t;
+    *tile_w = tw;
+  };
+  // few output channels over a stride-1 3x3 neighbourhood: the persistent
+  // kernel with resident weights where they fit, else the halo kernel
+  if (rows <= 64 && conv_resident_ok(kdt, a, rows <= 32 ? 32 : 64)) return use(rows <= 32 ? ConvTile::R32 : ConvTile::R64, 16);
+  if (rows <= 32 && conv_halo_ok(kdt, a)) return use(ConvTile::H32, 16);
+  if (a.transposed == 1 && hw > 0) {
+    // per-phase transposed convs: two phases (at most 128 outputs) or four
+    // (at most 64) per 256-column halo tile, once those fill the chip; fp8
+    // launches of at most one round of 128-column tiles take those (256 ->
+    // 128 at 90x160: 16.9 against 22.4; at 180x320 57.6 against 46.6, and in
+    // bf16 95 against 76, the generic tile 105)
+    if (rows <= 64 && m_tiles(hw) >= 200) return use(ConvTile::Q256, hw);
+    if (rows > 64 && rows <= 128)
+      return use(kdt == DType::FP8 && 4 * m_tiles(hw) <= 256 ? ConvTile::H128 : ConvTile::P256, hw);
+  }
+  if (!a.transposed && hw > 0 && rows > 64) {
+    // 3x3 stride-1 convs: with more than 128 outputs (the 256-channel
+    // chains) the two-group halo tile; 128-column halo tiles for at most 128
+    // outputs, and in fp8 for launches of one round of them (256 -> 256 at
+    // 90x160: 22.7 against 29.9; at 135x240, 270 workgroups, 45.8 against 33.9)
+    if (rows <= 128 || (kdt == DType::FP8 && m_tiles(hw) * ((rows + 127) / 128) <= 256))
+      return use(ConvTile::H128, hw);
+    return use(ConvTile::P256, hw);
+  }
+  if (!a.transposed && matrix16 && !a.out_f32 && rows <= 128 && a.cout % 8 == 0 && a.out_ld % 8 == 0) {
+    // convs over a few input channels (8 to 32): the persistent kernel with
+    // resident weights, narrowest N tile that holds the layer
+    const int bn = rows <= 32 ? 32 : (rows <= 64 ? 64 : 128);
+    if (conv_resident_s2_ok(kdt, a, bn))
+      return use(bn == 32 ? ConvTile::S32 : (bn == 64 ? ConvTile::S64 : ConvTile::S128), 16);
+  }
+  // wide layers on small grids: narrower tiles while their workgroups fit one
+  // round (fp8 128 -> 256, stride 2, 90x160 outputs: 64 columns 14.5, 128 17.4,
+  // 256 23.7; 180x320: 58, 38, 28)
+  if (matrix16 && rows > 64) {
+    const long t = m_tiles(*tile_w) * (a.transposed == 1 ? 4 : 1);
+    if (t * ((rows + 63) / 64) <= 256) return use(ConvTile::N64, *tile_w);
+    if (t * ((rows + 127) / 128) <= 256) return use(ConvTile::N128, *tile_w);
+  }
 }
 
 int conv_tile_width(int Ho, int Wo) {

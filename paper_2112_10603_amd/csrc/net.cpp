@@ -306,6 +306,12 @@ bool direct_layer(const Layer& L, DType dt) {
   return L.cin_pad % conv_k_step(dt) == 0;
 }
 
+size_t direct_bytes(const Layer& L, DType dt) {
+  const int bk = conv_k_step(dt), taps = L.mode == 1 ? 4 : 9;
+  const size_t rows = (size_t)(L.mode == 1 ? 4 : 1) * L.cout_pad;
+  return rows * ((L.cin_pad + bk - 1) / bk) * taps * bk * (dt == DType::F32 ? 6 : dtype_size(dt)) + kDirectPad;
+}
+
 std::vector<uint8_t> pack_direct(const Layer& L, DType dt) {
   if (dt != DType::F32) return fragment_order(L, dt, L.K_pad, pack_layer(L, dt));
   // fp32: three bf16 parts per scaled weight, exactly
@@ -313,7 +319,7 @@ std::vector<uint8_t> pack_direct(const Layer& L, DType dt) {
   const int k_pad = slices * taps * bk;
   const std::vector<float> p = pack_layer_f(L, bk, k_pad, L.w_host, true);
   const size_t rows = (size_t)(L.mode == 1 ? 4 : 1) * L.cout_pad;
-  std::vector<uint8_t> f(rows * k_pad * 6 + kDirectPad, 0);
+  std::vector<uint8_t> f(direct_bytes(L, dt), 0);
   uint16_t* q = reinterpret_cast<uint16_t*>(f.data());
   for (size_t r0 = 0; r0 < rows; r0 += 32)
     for (int st = 0; st < slices * taps; ++st)
@@ -621,85 +627,6 @@ Status Net::kernel_stats(const std::string& name, long* launches, double* ms, do
   return Status::ok();
 }
 
-namespace {
-
-// Block width (32, 16 or 8) of the halo tiles with the least padded area for
-// a launch, or 0 when the halo tiles cannot run it.
-int halo_default_width(DType dt, const ConvArgs& a0) {
-  int best = 0;
-  long best_area = -1;
-  for (int tw : {32, 16, 8}) {
-    ConvArgs a = a0;
-    a.tile_w = tw;
-    if (!conv_halo_tile_ok(dt, a)) continue;
-    const int th = 256 / tw;
-    const long area = (long)((a.Ho + th - 1) / th) * th * ((a.Wo + tw - 1) / tw) * tw;
-    if (best_area < 0 || area < best_area) {
-      best_area = area;
-      best = tw;
-    }
-  }
-  return best;
-}
-
-// Tile and pixel block width of a launch without a tuning entry (and not of
-// the direct-weight kernel). The figures are us per launch, one MI355X.
-void default_tile(DType kdt, const ConvArgs& a, ConvTile narrowest, ConvTile* tile, int* tile_w) {
-  const int rows = a.n_rows;
-  *tile = narrowest;  // the narrowest generic tile that holds the layer
-  *tile_w = conv_tile_width(a.Ho, a.Wo);
-  const bool matrix16 = kdt != DType::F32;
-  const int hw = matrix16 ? halo_default_width(kdt, a) : 0;  // 0: no halo tile runs it
-  auto m_tiles = [&](int tw) {
-    const int th = 256 / tw;
-    return (long)a.n_img * ((a.Ho + th - 1) / th) * ((a.Wo + tw - 1) / tw);
-  };
-  auto use = [&](ConvTile t, int tw) {
-    *tile = t;
-    *tile_w = tw;
-  };
-  // few output channels over a stride-1 3x3 neighbourhood: the persistent
-  // kernel with resident weights where they fit, else the halo kernel
-  if (rows <= 64 && conv_resident_ok(kdt, a, rows <= 32 ? 32 : 64)) return use(rows <= 32 ? ConvTile::R32 : ConvTile::R64, 16);
-  if (rows <= 32 && conv_halo_ok(kdt, a)) return use(ConvTile::H32, 16);
-  if (a.transposed == 1 && hw > 0) {
-    // per-phase transposed convs: two phases (at most 128 outputs) or four
-    // (at most 64) per 256-column halo tile, once those fill the chip; fp8
-    // launches of at most one round of 128-column tiles take those (256 ->
-    // 128 at 90x160: 16.9 against 22.4; at 180x320 57.6 against 46.6, and in
-    // bf16 95 against 76, the generic tile 105)
-    if (rows <= 64 && m_tiles(hw) >= 200) return use(ConvTile::Q256, hw);
-    if (rows > 64 && rows <= 128)
-      return use(kdt == DType::FP8 && 4 * m_tiles(hw) <= 256 ? ConvTile::H128 : ConvTile::P256, hw);
-  }
-  if (!a.transposed && hw > 0 && rows > 64) {
-    // 3x3 stride-1 convs: with more than 128 outputs (the 256-channel
-    // chains) the two-group halo tile; 128-column halo tiles for at most 128
-    // outputs, and in fp8 for launches of one round of them (256 -> 256 at
-    // 90x160: 22.7 against 29.9; at 135x240, 270 workgroups, 45.8 against 33.9)
-    if (rows <= 128 || (kdt == DType::FP8 && m_tiles(hw) * ((rows + 127) / 128) <= 256))
-      return use(ConvTile::H128, hw);
-    return use(ConvTile::P256, hw);
-  }
-  if (!a.transposed && matrix16 && !a.out_f32 && rows <= 128) {
-    // convs over a few input channels (8 to 32): the persistent kernel with
-    // resident weights, narrowest N tile that holds the layer
-    const int bn = rows <= 32 ? 32 : (rows <= 64 ? 64 : 128);
-    if (conv_resident_s2_ok(kdt, a, bn))
-      return use(bn == 32 ? ConvTile::S32 : (bn == 64 ? ConvTile::S64 : ConvTile::S128), 16);
-  }
-  // wide layers on small grids: narrower tiles while their workgroups fit one
-  // round (fp8 128 -> 256, stride 2, 90x160 outputs: 64 columns 14.5, 128 17.4,
-  // 256 23.7; 180x320: 58, 38, 28)
-  if (matrix16 && rows > 64) {
-    const long t = m_tiles(*tile_w) * (a.transposed == 1 ? 4 : 1);
-    if (t * ((rows + 63) / 64) <= 256) return use(ConvTile::N64, *tile_w);
-    if (t * ((rows + 127) / 128) <= 256) return use(ConvTile::N128, *tile_w);
-  }
-}
-
-}  // namespace
-
 Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long in_img_stride,
                  int Hi, int Wi, int n_img, void* out, int out_ld, long out_img_stride,
                  bool out_f32, bool accumulate, bool relu, bool in_fp8, bool out_fp8) {
@@ -745,7 +672,7 @@ Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long 
   a.zero = zero_;
   const DType kdt = in_fp8 ? DType::FP8 : dt_;
   // The table's choice, else the rules': the direct-weight kernel on small
-  // grids and for fp32 layers, default_tile() beyond. A table entry that was
+  // grids and for fp32 layers, conv_default_tile() beyond. A table entry that was
   // not timed against the direct kernel chooses among the other tiles only,
   // as does every entry of an fp32 layer (the direct kernel's sums differ from
   // the other tiles', and a view must not depend on its batch).
@@ -758,7 +685,7 @@ Status Net::conv(const Exec& x, const Layer& L, const void* in, int in_ld, long 
     Choice p{};
     int direct_w = 0;
     p.direct = conv_direct_tile(kdt, c, &direct_w);
-    default_tile(kdt, c, L.tile, &p.tile, &p.tile_w);
+    conv_default_tile(kdt, c, L.tile, &p.tile, &p.tile_w);
     auto it = tuned_.find(TuneKey{L.name, in_fp8 ? 1 : 0, c.Ho, c.Wo, c.n_img});
     if (it != tuned_.end() && it->second.tile != ConvTile::D) {
       p.tile = it->second.tile;

@@ -58,8 +58,10 @@ void plan_layer(Layer& L);
 // kernel reads it.
 std::vector<uint8_t> pack_layer(const Layer& L, DType dt);
 // Whether the direct kernel has a weight layout for a layer, and L.w_host in
-// that layout (fragment order, kDirectPad bytes of padding at the end).
+// that layout (fragment order, kDirectPad bytes of padding at the end) and its
+// size.
 bool direct_layer(const Layer& L, DType dt);
+size_t direct_bytes(const Layer& L, DType dt);
 std::vector<uint8_t> pack_direct(const Layer& L, DType dt);
 
 struct KernelStat {

@@ -9,11 +9,18 @@
 
 namespace ffv {
 
-// Device memory a call carves its buffers from (each 256-byte aligned):
-// base is a device address of cap bytes.
+// The default tile is the direct-weight kernel's only where its weights (up to
+// six bytes each, fp32) take at most this much, whatever the images: both entry
+// points then run the same kernel at every size.
+constexpr size_t kOpDirectBytes = (size_t)32 << 20;
+
+// Device memory a call carves its buffers from (each 256-byte aligned): base
+// is a device address of cap bytes, direct one of kOpDirectBytes for the
+// weights of the direct-weight kernel.
 struct OpConvScratch {
   void* base;
   size_t cap;
+  void* direct;
 };
 
 // One convolution layer as ffv_op_conv documents it. With scratch == null

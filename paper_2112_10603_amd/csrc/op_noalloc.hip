@@ -15,10 +15,16 @@ namespace {
 // its own copy, at its own address, until the process ends.
 constexpr size_t kScratchBytes = (size_t)FFV_OP_NOALLOC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// Weights of the direct-weight kernel: apart, so that the layers that fit the
+// array do not depend on the kernel that runs them.
+static __device__ __align__(256) unsigned char direct_weights[ffv::kOpDirectBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_mu;
-void* g_ptr[kMaxDevices] = {};  // device address of `scratch`, per device
+struct Arrays {
+  void *scratch, *direct;
+};
+Arrays g_ptr[kMaxDevices] = {};  // their device addresses, per device
 
 }  // namespace
 
@@ -29,20 +35,20 @@ extern "C" ffv_status ffv_op_conv_noalloc(int32_t precision, const float* x, int
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
     return ffv::op_fail(FFV_ERR_DEVICE, "no current HIP device");
-  void* base = nullptr;
+  Arrays at{};
   {
     std::lock_guard<std::mutex> lk(g_mu);
-    if (!g_ptr[dev]) {
-      // first call on this device (which is current): the array's device
-      // address; host code never uses the array's own name
-      void* p = nullptr;
-      const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-      if (e != hipSuccess || !p) return ffv::op_fail(FFV_ERR_DEVICE, hipGetErrorString(e));
-      g_ptr[dev] = p;
+    if (!g_ptr[dev].scratch) {
+      // first call on this device (which is current): the arrays' device
+      // addresses; host code never uses the arrays' own names
+      hipError_t e = hipGetSymbolAddress(&at.scratch, HIP_SYMBOL(scratch));
+      if (e == hipSuccess) e = hipGetSymbolAddress(&at.direct, HIP_SYMBOL(direct_weights));
+      if (e != hipSuccess || !at.scratch || !at.direct) return ffv::op_fail(FFV_ERR_DEVICE, hipGetErrorString(e));
+      g_ptr[dev] = at;
     }
-    base = g_ptr[dev];
+    at = g_ptr[dev];
   }
-  const ffv::OpConvScratch sc{base, kScratchBytes};
+  const ffv::OpConvScratch sc{at.scratch, kScratchBytes, at.direct};
   return ffv::op_conv_run(&sc, precision, x, n, cin, h, w, weight, bias, cout, stride, transposed, relu,
                           n_tile, tile_w, y, stream);
 }
