@@ -10,7 +10,9 @@
 // reads and writes past the caches (nothing is used twice). stitch_k: one
 // thread per output pixel in frame order, where a workgroup's pixels come
 // from several views; the other g keep it (g = 1, 2 and 8 measured 1 to 9 %
-// faster with it than in uncached strips), as do unaligned pointers.
+// faster with it than in uncached strips), as does g = 4 with a real view or a
+// frame that is not 16-byte aligned (its side views always are: both kernels
+// read them in 16-byte loads, and the entry point refuses others).
 // 1080 x 1920, g = 4 (896 MB): 177 -> 161 us (5.6 TB/s); cached loads in the
 // same strips take 172 us, two strips per workgroup 160.
 #include "common.h"
@@ -62,7 +64,7 @@ __global__ void stitch_k(StitchArgs a) {
 }
 
 // g = 4. Workgroups [0, sides): output row y of plane c of side view vi; the
-// rest: a row of a plane of the real view. Every pointer 16-byte aligned.
+// rest: a row of a plane of the real view. Every pointer is 16-byte aligned.
 __global__ __launch_bounds__(TPB) void strip4_k(StitchArgs a, int sides) {
   const long HW3 = 3L * a.H * a.W, HWs = (long)a.H * a.W;
   const int W3 = 3 * a.W;
@@ -97,8 +99,7 @@ __global__ __launch_bounds__(TPB) void strip4_k(StitchArgs a, int sides) {
 template <int G>
 hipError_t launch_g(const StitchArgs& a, hipStream_t s) {
   if constexpr (G == 4) {
-    uintptr_t bits = reinterpret_cast<uintptr_t>(a.hr) | reinterpret_cast<uintptr_t>(a.out);
-    for (int i = 0; i < 2 * a.n; ++i) bits |= reinterpret_cast<uintptr_t>(a.views[i]);
+    const uintptr_t bits = reinterpret_cast<uintptr_t>(a.hr) | reinterpret_cast<uintptr_t>(a.out);
     const long sides = 2L * a.n * 3 * (a.H / 4), blocks = sides + 3L * a.H;
     if (bits % 16 == 0 && a.W / 4 >= 64 && blocks <= 0x7fffffffL) {
       hipLaunchKernelGGL(strip4_k, dim3((unsigned)blocks), dim3(TPB), 0, s, a, (int)sides);
