@@ -534,7 +534,6 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void conv_direct(ConvArgs a, Dir
 
   // Whole runs of channels: fp32 four per store; bf16 and fp8 eight, the two
   // lane halves exchanging quads (half 0 takes the even group of a pair).
-  const bool out_f = a.out_f32 || F32;
   const bool runs = !merged && !a.accumulate && a.cout % 8 == 0 && a.out_ld % 8 == 0 &&
                     ((size_t)a.out & 15) == 0 && a.out_img_stride % 8 == 0 && (F32 || !a.out_f32);
 #pragma unroll
@@ -575,7 +574,6 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void conv_direct(ConvArgs a, Dir
             *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out) + pix + nb + 8 * g) =
                 make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
       } else {
-        (void)out_f;
         const int c0 = n0 + (wn * FN + j) * 32 + 8 * lhalf;  // this lane's run of the first pair
         if (a.out_scale) {
           uint32_t w[4];
