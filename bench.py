@@ -44,8 +44,9 @@ FP8_PSNR_DROP_DB = 27.09
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "conv_igemm_dense1080p_bf16_hbm_counters.md")
 MFMA_FILE = os.path.join(ROOT, "profiles", "conv_igemm_dense1080p_bf16_mfma_util.md")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2112_10603_amd", "csrc", f)
-                  for f in ("conv_kernel.h", "conv_halo.h", "conv_resident.h", "conv_resident_s2.h", "conv.hip",
-                            "pixel.hip")]
+                  for f in ("conv_kernel.h", "conv_halo.h", "conv_resident.h", "conv_resident_s2.h", "conv_direct.h",
+                            "conv_direct_bf16.hip", "conv_direct_f32.hip", "conv_direct_f8.hip", "conv.hip", "pixel.hip",
+                            "net.cpp")]
 
 
 def _counters_text(path=COUNTERS_FILE):

@@ -194,7 +194,8 @@ DirectTile conv_direct_tile(DType dt, const ConvArgs& a0, int* tile_w) {
     // 15.5, 32x32 (512) 15 / 17; 128 -> 5 at 64x64 9.5 / 18. So up to 512
     // workgroups. Whether the sum is in parts goes by one image; a launch of
     // more images takes the tiles that add the same parts in turn (3 to 10 %
-    // slower than those that need not).
+    // slower than those that need not). (fp32 times here and below are of
+    // unscaled operands: the scaling added 2 to 6 % to every tile.)
     if (a0.cin_pad > 32 && (a0.transposed != 2 || a0.cout <= 32)) {
       n = blocks(m32n32k, &tw);
       const long n1 = a0.n_img > 0 ? n / a0.n_img : 0;

@@ -32,16 +32,22 @@
 //
 // What bounds it. Small grids: the chain of a workgroup's K rounds (144 for
 // 256 channels): dependent MFMAs are 64 cycles apart, 3.8 us in all, and about
-// 4.5 us go to the launch, the first slice and the epilogue; 256 -> 256 at 45x80 takes 10 us where the tiles of conv_kernel.h
-// take 15 to 65 (a barrier and a full load latency per K step). An fp32 round
-// is five dependent MFMAs and the splitting of its activations, so small
-// fp32 images share a tile's K sum among eight waves (KS): 256 -> 256 at
-// 32x32 27 -> 12 us, at 8x8 26 -> 10. Larger fp32 launches: the
-// matrix cores and power; 256 -> 256 at 270x480 takes 823 us = 186 TFLOP/s
-// (1255 us on fp32 MFMA), MFMA pipes 68 % busy at 1.69 GHz, the rest being
-// weight-load waits (14 %), the first slice of each workgroup and the
+// 4.5 us go to the launch, the first slice and the epilogue; bf16 256 -> 256 at
+// 45x80 takes 10 us where the tiles of conv_kernel.h take 15 to 65 (a barrier
+// and a full load latency per K step). An fp32 round is five dependent MFMAs
+// and the splitting of its activations, so small fp32 images share a tile's K
+// sum among eight waves (KS): 256 -> 256 at 32x32 27 -> 12 us, at 8x8 26 -> 10.
+// Larger fp32 launches: the matrix cores and power; 256 -> 256 at 270x480 took
+// 823 us (1255 us on fp32 MFMA), MFMA pipes 68 % busy at 1.69 GHz, the rest
+// being weight-load waits (14 %), the first slice of each workgroup and the
 // epilogue. The split's VALU work runs in the shadow of the MFMAs: before it
-// was interleaved by hand, the same launch took 935 us.
+// was interleaved by hand, the same launch took 935 us. Those fp32 figures are
+// of unscaled operands; the scaling adds two multiplications to the 13
+// instructions that split a pair, 1.5 % where a wave has four MFMAs per split
+// (90x160 87.0 -> 88.3 us) and up to 6 % where it has one (45x80 33.2 -> 35.2).
+// With it, by kernel trace on another card: 270x480 724 us = 211 TFLOP/s, on
+// fp32 MFMA 1300. (Scaling once per slice in LDS cost 4 to 9 % of a view: a
+// read, a multiplication and a write in a row at the slice's barrier.)
 #pragma once
 
 #include "conv_kernel.h"

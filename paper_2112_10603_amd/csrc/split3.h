@@ -1,6 +1,8 @@
 // The exact split of a float into three bf16 parts, x = h + m + l (8 + 8 + 8
 // significand bits, each the rest rounded to nearest even), with which fp32
-// convolutions run on the bf16 matrix cores. Host side: the packed weights.
+// convolutions run on the bf16 matrix cores (the method of Henry, Tang and
+// Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
+// Higher-Precision Computations", ARITH 2019). Host side: the packed weights.
 // Weights and activations are both scaled by 2^24 before they are split: the
 // last bit of the smallest float, 2^-149, becomes 2^-125, so every non-zero
 // part of every value is a normal bf16 number and the split is exact over the
