@@ -32,8 +32,8 @@
 // its neighbour) and writes one partial; one workgroup per image sums them in
 // a fixed order in double, so the result does not depend on scheduling.
 //
-// Measured (one MI355X, whole call): 8 x 3 x 256 x 448 with gradient 561 ->
-// 84 us, 1 x 3 x 1079 x 1917 without 2632 -> 73 us. (The bands formed in the
+// Measured (one MI355X, whole call): 8 x 3 x 256 x 448 with gradient 545 ->
+// 83 us, 1 x 3 x 1079 x 1917 without 2627 -> 74 us. (The bands formed in the
 // tiles of the reduce passes, which saves their second read, took 90 and 75:
 // the tiles' LDS work outweighs a read that hits the caches.) Before, one thread
 // summed all partials of an image, each level had its own launches, seeds
